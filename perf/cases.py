@@ -43,7 +43,7 @@ def listed():
         # the small correctness system, solved to the tolerance: every kernel is
         # a few microseconds, the whole call is launches and their latency
         dict(name="poisson2d_64_tol", kind="solve", system="poisson2d", nx=64, ny=64, nz=1,
-             fmt="fp64", pc="none", restart=100, steps=184, tol=1e-10),
+             fmt="fp64", pc="none", restart=100, steps=340, tol=1e-10),
         # a small system of the smoke check's size, short restarts, Jacobi
         dict(name="convdiff7_16_jacobi", kind="solve", system="convdiff7", nx=16, ny=16, nz=16,
              fmt="fp16", pc="jacobi", restart=30, steps=60, tol=0.0),
@@ -221,11 +221,12 @@ def _rhs(n, seed):
 
 def _params(seed):
     """The network as it is in the middle of training: the initial weights
-    with a small random last layer and small biases."""
+    with a small random last layer and small biases (corrections of a few
+    percent of the Jacobi rows)."""
     model = LearnedSPAI(DEV, seed)
     z = torch.randn(NPARAM, dtype=torch.float32, device=DEV, generator=_gen(seed, 4))
     w3 = NF * NH + NH + NH * NH + NH
-    model.params[w3:] = 0.02 * z[w3:]
+    model.params[w3:] = 0.002 * z[w3:]
     model.params[NF * NH:NF * NH + NH] = 0.02 * z[NF * NH:NF * NH + NH]
     cbg.spai_round_weights(model.params, model.weights)
     return model
