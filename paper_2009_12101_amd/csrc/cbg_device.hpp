@@ -87,9 +87,9 @@ struct EncParam {
 template <int F> struct Fmt;
 
 // VW entries per 16-byte chunk, CH chunks per thread and tile, KC stored
-// vectors per multi-dot batch, UNR vectors in flight in the update loop.
+// vectors per multi-dot batch.
 template <> struct Fmt<F_FP64> {
-    static constexpr int VW = 2, CH = 4, KC = 4, UNR = 2;
+    static constexpr int VW = 2, CH = 4, KC = 4;
     static constexpr bool SCALED = false;
     __device__ static void dec(u32x4 q, double, double *d)
     {
@@ -105,7 +105,7 @@ template <> struct Fmt<F_FP64> {
 };
 
 template <> struct Fmt<F_FP32> {
-    static constexpr int VW = 4, CH = 2, KC = 8, UNR = 4;
+    static constexpr int VW = 4, CH = 2, KC = 8;
     static constexpr bool SCALED = false;
     __device__ static void dec(u32x4 q, double, double *d)
     {
@@ -124,14 +124,11 @@ template <> struct Fmt<F_FP32> {
 #ifndef CBG_KC16
 #define CBG_KC16 4
 #endif
-#ifndef CBG_UNR16
-#define CBG_UNR16 2
-#endif
 #ifndef CBG_CH16
 #define CBG_CH16 2
 #endif
 template <int F> struct Fmt16 {
-    static constexpr int VW = 8, CH = CBG_CH16, KC = CBG_KC16, UNR = CBG_UNR16;
+    static constexpr int VW = 8, CH = CBG_CH16, KC = CBG_KC16;
     static constexpr bool SCALED = (F == F_INT16 || F == F_FP16S);
     __device__ static double one(uint32_t c, double s)
     {
@@ -178,7 +175,7 @@ template <> struct Fmt<F_INT16> : Fmt16<F_INT16> {};
 template <> struct Fmt<F_FP16S> : Fmt16<F_FP16S> {};
 
 template <> struct Fmt<F_INT32> {
-    static constexpr int VW = 4, CH = 2, KC = 8, UNR = 4;
+    static constexpr int VW = 4, CH = 2, KC = 8;
     static constexpr bool SCALED = true;
     __device__ static void dec(u32x4 q, double s, double *d)
     {
@@ -199,7 +196,7 @@ template <> struct Fmt<F_INT32> {
 };
 
 template <> struct Fmt<F_E4M3> {
-    static constexpr int VW = 16, CH = 1, KC = 4, UNR = 2;
+    static constexpr int VW = 16, CH = 1, KC = 4;
     static constexpr bool SCALED = true;
     __device__ static void dec(u32x4 q, double s, double *d)
     {

@@ -18,6 +18,9 @@
 // The host only enqueues kernels; it synchronises once per restart cycle.
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+#include <type_traits>
+
 #include "cbg_device.hpp"
 #include "cbg_launch.hpp"
 
@@ -1039,54 +1042,130 @@ __global__ void k_fill_i32(int32_t *p, int count, int32_t v)
 // ---------------------------------------------------------------------------
 
 
-template <int F>
-__device__ __forceinline__ u32x4 ld_chunk(const uint8_t *__restrict__ V, int64_t ldb, int k,
-                                          int64_t i0)
-{
-    return __builtin_nontemporal_load(
-        (const u32x4 *)(V + (int64_t)k * ldb + i0 * fmt_bytes(F)));
-}
+// A block's tile of the stored vectors: BLK * VW * CH consecutive rows, chunk
+// c of a thread at byte voff[c] of the tile.  Every load is a 16-byte buffer
+// load on a resource that covers the tile of one vector: base, vector and
+// range are scalars, a vector that does not exist (k >= j) has range 0 and
+// reads as code 0 without touching memory, and a whole batch issues without
+// a branch.  In the ragged last tile a chunk that starts at or beyond n
+// reads the tile's first chunk instead (in bounds, since a chunk that starts
+// below n lies inside the leading dimension, a multiple of 16) and keep()
+// clears the bytes of entries >= n, so that tile streams like any other:
+// with its loads guarded one by one it took a round trip per vector (update
+// at 538,650 int16 rows, j = 50: 59 us, 22 us now).
+constexpr int BUF_NT = 2;           // cache policy of streamed data: non-temporal
+
+// Buffer resource word 3 for raw 32-bit accesses on gfx9-family parts.
+constexpr int BUF_RSRC_W3 = 0x00020000;
+
+template <int F> struct VecTile {
+    static constexpr int VW = Fmt<F>::VW, CH = Fmt<F>::CH;
+    static constexpr int ROWS = BLK * VW * CH, BYTES = ROWS * fmt_bytes(F);
+    const uint8_t *base;            // the tile in vector 0
+    int64_t ldb;                    // bytes between vectors
+    int64_t row0;
+    uint32_t voff[CH];
+    bool full;                      // every row of the tile is below n
+
+    __device__ __forceinline__ void set(const uint8_t *V, int64_t ldb_, int64_t tile, int64_t n)
+    {
+        row0 = tile * ROWS;
+        base = V + tile * BYTES;
+        ldb = ldb_;
+        full = row0 + ROWS <= n;
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+            voff[c] = full || row(c) < n ? (uint32_t)(c * BLK + threadIdx.x) * 16u : 0u;
+    }
+    __device__ __forceinline__ int64_t row(int c) const
+    {
+        return row0 + ((int64_t)c * BLK + threadIdx.x) * VW;
+    }
+    // chunk c of vector k (code 0 for k >= j)
+    __device__ __forceinline__ u32x4 load(int k, int j, int c) const
+    {
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)(base + (int64_t)k * ldb), 0, k < j ? BYTES : 0, BUF_RSRC_W3);
+        return __builtin_amdgcn_raw_buffer_load_b128(r, voff[c], 0, BUF_NT);
+    }
+    // the chunk, in a ragged tile (FULL false) with the bytes of entries >= n
+    // cleared (code 0)
+    template <bool FULL>
+    __device__ __forceinline__ u32x4 keep(u32x4 q, int c, int64_t n) const
+    {
+        if constexpr (!FULL) {
+            const int64_t left = n - row(c);
+            const int b = left <= 0 ? 0 : left >= VW ? 16 : (int)left * fmt_bytes(F);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const int m = b - 4 * d;         // bytes kept of word d
+                q[d] &= m >= 4 ? ~0u : m <= 0 ? 0u : (1u << (8 * m)) - 1u;
+            }
+        }
+        return q;
+    }
+};
 
 // GRAM: the same pass also forms g_k = dec(V_k)^T dec(V_{j-1}), k < j, the
 // newest row of the Gram matrix of the stored vectors (partials in rows
 // j + 2 + k), from a register tile of the newest vector.
+//
+// blockIdx.y takes the stored vectors [y kchunk, (y + 1) kchunk) (kchunk a
+// multiple of KC, or j): HBM-bound once the loads of some 512 blocks are in
+// flight, latency-bound below that, and a vector length gives only
+// n / TILE tiles (132 on 538,650 fp16 rows).  Each value is still summed
+// over one tile by one block in the same order, so the partials and the
+// sums keep their bits whatever the split; a chunk reads its tile of w
+// again (from L2).  multidot_shape chooses the split.
 template <int F, bool GRAM>
 __global__ __launch_bounds__(BLK) CBG_MD_ATTR void k_multidot(const uint8_t *__restrict__ V, int64_t ld,
                                                   const double *__restrict__ scales, int n, int j,
                                                   const double *__restrict__ w, RedArgs ra,
-                                                  const DevState *st, int gated, int with_norms)
+                                                  const DevState *st, int gated, int with_norms,
+                                                  int kchunk)
 {
     if (gated && st->done)
         return;
     using T = Fmt<F>;
+    using Tile = VecTile<F>;
     constexpr int VW = T::VW, CH = T::CH, KC = T::KC;
     constexpr int NV = GRAM ? 2 : 1;                  // values per stored vector
     constexpr int WROW = MAX_RESTART + 1;
-    constexpr int TILE = BLK * VW * CH;
     const int64_t ldb = ld * fmt_bytes(F);
     // per-wave running sums over the block's tiles: no barrier until the end
     __shared__ double wacc[NWAVE][NV * WROW];
-    for (int k = threadIdx.x; k < NWAVE * NV * WROW; k += BLK)
-        (&wacc[0][0])[k] = 0.0;
+    const int kb = (int)blockIdx.y * kchunk, ke = min(kb + kchunk, j);  // this block's vectors
+    for (int k = kb + (int)threadIdx.x; k < ke; k += BLK)
+#pragma unroll
+        for (int q = 0; q < NWAVE; ++q)
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+                wacc[q][v * WROW + k] = 0.0;
     __syncthreads();
-    const int64_t ntiles = ((int64_t)n + TILE - 1) / TILE;
+    if (blockIdx.y > 0)
+        with_norms = 0;                               // the first chunk's blocks form them
+    const int64_t ntiles = ((int64_t)n + Tile::ROWS - 1) / Tile::ROWS;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double ssq = 0.0, mx = 0.0;
     for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const bool full = (tile + 1) * TILE <= n;
+        Tile vt;
+        vt.set(V, ldb, tile, n);
         double wr[CH * VW];
         double gr[GRAM ? CH * VW : 1];
-        int64_t i0[CH];
+        u32x4 newest[GRAM ? CH : 1];
+        if constexpr (GRAM) {
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            i0[c] = tile * TILE + ((int64_t)c * BLK + threadIdx.x) * VW;
-            load_w<VW>(w, n, i0[c], wr + c * VW);
+            for (int c = 0; c < CH; ++c)
+                newest[c] = vt.load(j - 1, j, c);
         }
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+            load_w<VW>(w, n, vt.row(c), wr + c * VW);
         if constexpr (GRAM) {
             const double sg = T::SCALED ? scales[j - 1] : 1.0;
 #pragma unroll
             for (int c = 0; c < CH; ++c)
-                load_dec<F>(V + (int64_t)(j - 1) * ldb, i0[c], n, sg, gr + c * VW);
+                T::dec(vt.template keep<false>(newest[c], c, n), sg, gr + c * VW);
         }
         if (with_norms) {
 #pragma unroll
@@ -1095,15 +1174,15 @@ __global__ __launch_bounds__(BLK) CBG_MD_ATTR void k_multidot(const uint8_t *__r
                 mx = fmax(mx, fabs(wr[e]));
             }
         }
-        for (int kc = 0; kc < j; kc += KC) {
-            double acc[NV * KC];
-            if (full) {
+        auto stream = [&](auto whole) __attribute__((always_inline)) {
+            for (int kc = kb; kc < ke; kc += KC) {
+                double acc[NV * KC];
                 u32x4 raw[KC][CH];
 #pragma unroll
                 for (int kk = 0; kk < KC; ++kk)
 #pragma unroll
                     for (int c = 0; c < CH; ++c)
-                        raw[kk][c] = ld_chunk<F>(V, ldb, min(kc + kk, j - 1), i0[c]);
+                        raw[kk][c] = vt.load(kc + kk, j, c);
                 // keep the batch's loads together, ahead of its arithmetic: under
                 // the Gram tile's register pressure the scheduler would otherwise
                 // interleave them with the FMAs, one load in flight per wave
@@ -1115,7 +1194,8 @@ __global__ __launch_bounds__(BLK) CBG_MD_ATTR void k_multidot(const uint8_t *__r
 #pragma unroll
                     for (int c = 0; c < CH; ++c) {
                         double d[VW];
-                        T::dec(raw[kk][c], s, d);
+                        T::dec(vt.template keep<decltype(whole)::value>(
+                                    raw[kk][c], c, n), s, d);
 #pragma unroll
                         for (int e = 0; e < VW; ++e) {
                             a = fma(d[e], wr[c * VW + e], a);
@@ -1127,46 +1207,30 @@ __global__ __launch_bounds__(BLK) CBG_MD_ATTR void k_multidot(const uint8_t *__r
                     if constexpr (GRAM)
                         acc[KC + kk] = g;
                 }
-            } else {
-#pragma unroll
-                for (int kk = 0; kk < KC; ++kk) {
-                    const int k = min(kc + kk, j - 1);
-                    const double s = T::SCALED ? scales[k] : 1.0;
-                    const uint8_t *Vk = V + (int64_t)k * ldb;
-                    double a = 0.0, g = 0.0;
-#pragma unroll
-                    for (int c = 0; c < CH; ++c) {
-                        double d[VW];
-                        load_dec<F>(Vk, i0[c], n, s, d);
-#pragma unroll
-                        for (int e = 0; e < VW; ++e) {
-                            a = fma(d[e], wr[c * VW + e], a);
-                            if constexpr (GRAM)
-                                g = fma(d[e], gr[c * VW + e], g);
-                        }
-                    }
-                    acc[kk] = a;
-                    if constexpr (GRAM)
-                        acc[KC + kk] = g;
+                wave_transpose_sum<NV * KC>(acc);
+                if (lane < NV * KC) {
+                    const int idx = bitrev<NV * KC>(lane);
+                    const int k = kc + (idx < KC ? idx : idx - KC);
+                    if (k < ke)
+                        wacc[wave][(idx < KC ? 0 : WROW) + k] += acc[0];
                 }
             }
-            wave_transpose_sum<NV * KC>(acc);
-            if (lane < NV * KC) {
-                const int idx = bitrev<NV * KC>(lane);
-                const int k = kc + (idx < KC ? idx : idx - KC);
-                if (k < j)
-                    wacc[wave][(idx < KC ? 0 : WROW) + k] += acc[0];
-            }
-        }
+        };
+        if (vt.full)
+            stream(std::true_type{});
+        else
+            stream(std::false_type{});
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < NV * j; k += BLK) {
-        const int src = k < j ? k : WROW + (k - j);
+    const int nk = ke - kb;
+    for (int e = threadIdx.x; e < NV * nk; e += BLK) {
+        const int v = e < nk ? 0 : 1, k = kb + e - v * nk;
+        const int src = v * WROW + k;
         double t = wacc[0][src];
 #pragma unroll
         for (int q = 1; q < NWAVE; ++q)
             t += wacc[q][src];
-        const int row = k < j ? k : j + 2 + (k - j);       // g_k in row j + 2 + k
+        const int row = v == 0 ? k : j + 2 + k;            // g_k in row j + 2 + k
         ra.part[(size_t)row * ra.stride + blockIdx.x] = t;
     }
     if (with_norms) {
@@ -1266,13 +1330,14 @@ constexpr int HARD_BLOCKS = 256;
 // as one FMA chain.  The NK columns of a row are loaded together and UL
 // rows at a time (column indices clamped into [0, j); the extra sums are
 // not stored), so a wave keeps NK * UL loads of G in flight instead of
-// walking its columns one after another.
-template <int NK>
+// walking its columns one after another; LOADS (a multiple of 8) is about
+// how many.
+template <int NK, int LOADS>
 __device__ __forceinline__ void gram_times_h(const double *__restrict__ G, size_t ldg,
                                              const double *lh, int j, int l0, int l1, int lane,
                                              double *out)
 {
-    constexpr int UL = NK == 1 ? 8 : NK == 2 ? 4 : NK == 3 ? 3 : 2;
+    constexpr int UL = LOADS / 8 * (NK == 1 ? 8 : NK == 2 ? 4 : NK == 3 ? 3 : 2);
     int kc[NK];
     double acc[NK];
 #pragma unroll
@@ -1308,7 +1373,18 @@ __device__ __forceinline__ void gram_times_h(const double *__restrict__ G, size_
             out[lane + 64 * q] = acc[q];
 }
 
-template <int F, int ROLE>
+// The stored vectors stream through a ring of RING batches of UNR vectors:
+// a batch's registers are reloaded, RING batches ahead, as soon as it has
+// been added, so the other batches are in flight all the time, and the whole
+// ring already while the one-pass prologue forms u.  (Two buffers swapped by
+// a register copy waited for every load of the next batch before adding it.)
+// The coefficients and scales come from LDS.  DEEP rings hold 16 loads per
+// lane, for grids that do not fill the chip, where the time is the latency
+// of a block's own loads (528,000 rows of int16, 132 tiles, j to 50: 33 us
+// before, 15 us deep, 19 us shallow); shallow rings hold 4 (8 in fp64), which
+// keeps the blocks of a full grid closer together in the basis: at 128^3
+// fp16, 512 tiles, j to 100, 43.7 us shallow, 49.3 us deep, 43.2 us before.
+template <int F, int ROLE, bool DEEP>
 __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, int64_t ld,
                                                 const double *__restrict__ scales, int n, int j_arg,
                                                 const double *__restrict__ coef,
@@ -1332,12 +1408,28 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
     if constexpr (ROLE == U_SOLUTION || ROLE == U_COMBINE)
         j = st->jeff;
     using T = Fmt<F>;
-    constexpr int VW = T::VW, CH = T::CH, UNR = T::UNR;
-    constexpr int TILE = BLK * VW * CH;
+    using Tile = VecTile<F>;
+    constexpr int VW = T::VW, CH = T::CH, UNR = DEEP ? 4 / CH : CH == 1 ? 2 : 1;
+    constexpr int RING = DEEP ? 4 : 2;
     const int64_t ldb = ld * fmt_bytes(F);
-    const int64_t ntiles = ((int64_t)n + TILE - 1) / TILE;
+    const int64_t ntiles = ((int64_t)n + Tile::ROWS - 1) / Tile::ROWS;
     double ssq = 0.0, mx = 0.0;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    Tile vt;
+    u32x4 ring[RING][UNR][CH];
+    auto load_batch = [&](int r, int k0) {
+#pragma unroll
+        for (int u = 0; u < UNR; ++u)
+#pragma unroll
+            for (int c = 0; c < CH; ++c)
+                ring[r][u][c] = vt.load(k0 + u, j, c);
+    };
+    auto start_tile = [&](int64_t tile) {
+        vt.set(V, ldb, tile, n);
+#pragma unroll
+        for (int r = 0; r < RING; ++r)
+            load_batch(r, r * UNR);
+    };
     // U_CGS2: Gram-form re-dot u = h - G h, then steps 5-10 in one update;
     // U_HARD: the explicit second pass of a hard step.  lp holds partial sums
     // of G h in the prologue and, on a hard step, the per-wave re-dot sums.
@@ -1347,7 +1439,9 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
     // 0 .. j-2 into H, the carry into the state) while the other blocks
     // stream the basis, which leaves the closing fold only the new rotation.
     constexpr bool ONEPASS = ROLE == U_CGS2 || ROLE == U_HARD;
-    __shared__ double lc[ONEPASS ? MAX_RESTART : 1];
+    // coefficients and scales, the coefficients 0 up to a whole batch beyond j
+    // (the kernel-level calls take one vector more than a solve's restart)
+    __shared__ double lc[MAX_RESTART + 1 + UNR], lsc[T::SCALED ? MAX_RESTART + 1 + UNR : 1];
     __shared__ double lh[ONEPASS ? MAX_RESTART : 1];
     __shared__ double lp[ONEPASS ? NWAVE * MAX_RESTART : 1];
     __shared__ double lr[2][NWAVE];
@@ -1361,6 +1455,11 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
         if (tid == 0)
             stw->carry = carry;
     };
+    if ((int)blockIdx.x < ntb && blockIdx.x < ntiles)
+        start_tile(blockIdx.x);
+    if constexpr (T::SCALED)
+        for (int k = tid; k < j + UNR; k += BLK)
+            lsc[k] = k < j ? scales[k] : 1.0;
     bool hard = false;
     if constexpr (ROLE == U_CGS2) {
         // Every block forms the same u = h - G h (G symmetric: wave wv sums
@@ -1376,14 +1475,16 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
         const size_t ldg = (size_t)st->m + 1;
         const int q = (j + NWAVE - 1) / NWAVE;
         const int l0 = min(wv * q, j), l1 = min(l0 + q, j);
+        constexpr int GL = 16;
+        double *lpw = lp + wv * MAX_RESTART;
         switch ((j + 63) / 64) {
-        case 1: gram_times_h<1>(G, ldg, lh, j, l0, l1, lane, lp + wv * MAX_RESTART); break;
-        case 2: gram_times_h<2>(G, ldg, lh, j, l0, l1, lane, lp + wv * MAX_RESTART); break;
-        case 3: gram_times_h<3>(G, ldg, lh, j, l0, l1, lane, lp + wv * MAX_RESTART); break;
-        case 4: gram_times_h<4>(G, ldg, lh, j, l0, l1, lane, lp + wv * MAX_RESTART); break;
+        case 1: gram_times_h<1, GL>(G, ldg, lh, j, l0, l1, lane, lpw); break;
+        case 2: gram_times_h<2, GL>(G, ldg, lh, j, l0, l1, lane, lpw); break;
+        case 3: gram_times_h<3, GL>(G, ldg, lh, j, l0, l1, lane, lpw); break;
+        case 4: gram_times_h<4, GL>(G, ldg, lh, j, l0, l1, lane, lpw); break;
         default:
             for (int k0 = 0; k0 < j; k0 += 256)
-                gram_times_h<4>(G + k0, ldg, lh, j - k0, l0, l1, lane, lp + wv * MAX_RESTART + k0);
+                gram_times_h<4, GL>(G + k0, ldg, lh, j - k0, l0, l1, lane, lpw + k0);
             break;
         }
         __syncthreads();
@@ -1442,8 +1543,6 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
             for (int k = tid; k < NWAVE * j; k += BLK)
                 lp[k] = 0.0;
         }
-        __syncthreads();
-        coef = lc;
     }
     if constexpr (ROLE == U_HARD) {
         // The hard step's explicit second pass.  Every block folds, from the
@@ -1484,67 +1583,63 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
         }
         if (!ro)
             return;
-        coef = lc;
     }
+    if constexpr (!ONEPASS)
+        for (int k = tid; k < j; k += BLK)
+            lc[k] = coef[k];
+    if (tid < UNR)
+        lc[j + tid] = 0.0;
+    __syncthreads();
     for (int64_t tile = blockIdx.x; tile < ntiles; tile += ntb) {
-        const bool full = (tile + 1) * TILE <= n;
+        if (tile != blockIdx.x)
+            start_tile(tile);
         double s[CH * VW];
         int64_t i0[CH];
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            i0[c] = tile * TILE + ((int64_t)c * BLK + threadIdx.x) * VW;
+            i0[c] = vt.row(c);
 #pragma unroll
             for (int e = 0; e < VW; ++e)
                 s[c * VW + e] = 0.0;
         }
-        if (full && j > 0) {
-            u32x4 cur[UNR][CH];
+        auto add = [&](int r, int k0) __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < UNR; ++u)
-#pragma unroll
-                for (int c = 0; c < CH; ++c)
-                    cur[u][c] = ld_chunk<F>(V, ldb, min(u, j - 1), i0[c]);
-            for (int kg = 0; kg < j; kg += UNR) {
-                u32x4 nxt[UNR][CH];
-#pragma unroll
-                for (int u = 0; u < UNR; ++u)
-#pragma unroll
-                    for (int c = 0; c < CH; ++c)
-                        nxt[u][c] = ld_chunk<F>(V, ldb, min(kg + UNR + u, j - 1), i0[c]);
-#pragma unroll
-                for (int u = 0; u < UNR; ++u) {
-                    const int k = min(kg + u, j - 1);
-                    const double ck = (kg + u < j) ? coef[k] : 0.0;
-                    const double sk = T::SCALED ? scales[k] : 1.0;
-#pragma unroll
-                    for (int c = 0; c < CH; ++c) {
-                        double d[VW];
-                        T::dec(cur[u][c], sk, d);
-#pragma unroll
-                        for (int e = 0; e < VW; ++e)
-                            s[c * VW + e] = fma(ck, d[e], s[c * VW + e]);
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < UNR; ++u)
-#pragma unroll
-                    for (int c = 0; c < CH; ++c)
-                        cur[u][c] = nxt[u][c];
-            }
-        } else {
-            for (int k = 0; k < j; ++k) {
-                const double ck = coef[k];
-                const double sk = T::SCALED ? scales[k] : 1.0;
-                const uint8_t *Vk = V + (int64_t)k * ldb;
+            for (int u = 0; u < UNR; ++u) {
+                const double ck = lc[k0 + u];
+                const double sk = T::SCALED ? lsc[k0 + u] : 1.0;
 #pragma unroll
                 for (int c = 0; c < CH; ++c) {
                     double d[VW];
-                    load_dec<F>(Vk, i0[c], n, sk, d);
+                    T::dec(ring[r][u][c], sk, d);
 #pragma unroll
                     for (int e = 0; e < VW; ++e)
                         s[c * VW + e] = fma(ck, d[e], s[c * VW + e]);
                 }
             }
+        };
+        int k0 = 0;
+        for (; k0 + RING * UNR <= j; k0 += RING * UNR) {
+#pragma unroll
+            for (int r = 0; r < RING; ++r) {
+                add(r, k0 + r * UNR);
+                load_batch(r, k0 + (RING + r) * UNR);
+                // a batch's loads leave before the next batch's arithmetic (the
+                // scheduler would gather them at the end of the ring)
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < RING; ++r)
+            if (k0 + r * UNR < j)
+                add(r, k0 + r * UNR);
+        if (!vt.full) {
+            // rows >= n took whatever their chunk holds
+#pragma unroll
+            for (int c = 0; c < CH; ++c)
+#pragma unroll
+                for (int e = 0; e < VW; ++e)
+                    if (i0[c] + e >= n)
+                        s[c * VW + e] = 0.0;
         }
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
@@ -1714,9 +1809,6 @@ __device__ __forceinline__ void store_wn(double *__restrict__ w, int64_t n, int6
 }
 
 constexpr int FUSED_JMAX = 104;     // largest j the fused pass takes
-
-// Buffer resource word 3 for raw 32-bit accesses on gfx9-family parts.
-constexpr int BUF_RSRC_W3 = 0x00020000;
 
 template <int F, int JM>
 __global__ __launch_bounds__(BLK) void k_update_redot(const uint8_t *__restrict__ V, int64_t ld,
@@ -2871,23 +2963,66 @@ int orth_grid(int fmt, int64_t n)
     return grid_for(n, tile);
 }
 
+// The multi-dot's launch: how many stored vectors a block takes (a multiple
+// of the batch kc), and LDS padding that limits a CU to two blocks.  Three
+// blocks fit a CU by registers.  Up to 512 blocks the time is set by the
+// slowest block's loads, so more, shorter blocks win; beyond three per CU the
+// blocks run in rounds, each as long as its blocks.  Each block reads its
+// tile of w (and of the newest vector) besides its chunk, `extra` vectors'
+// worth.  The choice minimises rounds x blocks per round x vectors per block:
+// 132 int16 tiles at j = 50 run in 4 chunks (34 us before, 11 us now); 1000
+// fp16 tiles at j to 200 in one chunk, two per CU (two even rounds, 138 us;
+// three per CU leave a second round of 232 blocks, 154 us; before 141 us).
+constexpr int FULL_GRID = 512;
+struct MdotShape {
+    int chunk, pad;
+};
+static MdotShape multidot_shape(int tiles, int j, int kc, int eb)
+{
+    constexpr int SLOTS = 768, PAD = 24576;
+    const int batches = (j + kc - 1) / kc;
+    const double extra = 1.0 + 8.0 / eb;
+    MdotShape best{batches * kc, 0};
+    double cost = 1e300;
+    for (int s = 1; s <= batches; ++s) {
+        const int per = (batches + s - 1) / s;
+        const int blocks = tiles * ((batches + per - 1) / per);
+        const double work = per * kc + extra;
+        const double c = blocks <= SLOTS
+                             ? std::max(blocks, FULL_GRID) * work
+                             : (double)((blocks + SLOTS - 1) / SLOTS) * SLOTS * work;
+        if (c < cost) {
+            cost = c;
+            best = {per * kc, 0};
+        }
+    }
+    const double two = (double)((tiles + FULL_GRID - 1) / FULL_GRID) * FULL_GRID *
+                       (batches * kc + extra);
+    if (two < cost)
+        best = {batches * kc, PAD};
+    return best;
+}
+
 // With events, the launch goes through hipExtLaunchKernelGGL, which records
 // them at the kernel's own start and end (the interval a profiler reports).
 void launch_multidot(const OrthArgs &a, hipStream_t s)
 {
-    int g = orth_grid(a.fmt, a.n);
+    const int tiles = orth_grid(a.fmt, a.n);
+    MdotShape sh{};
+    CBG_FMT_SWITCH(a.fmt, (sh = multidot_shape(tiles, a.j, Fmt<F>::KC, fmt_bytes(F))))
+    const dim3 g(tiles, (a.j + sh.chunk - 1) / sh.chunk);
     RedArgs ra{a.ws.orth, a.ws.stride};
     const uint8_t *V = (const uint8_t *)a.V;
 #define CBG_MD(G)                                                                              \
     if (a.ev0) {                                                                               \
-        CBG_FMT_SWITCH(a.fmt, (hipExtLaunchKernelGGL(k_multidot<F, G>, dim3(g), dim3(BLK), 0, s, \
+        CBG_FMT_SWITCH(a.fmt, (hipExtLaunchKernelGGL(k_multidot<F, G>, g, dim3(BLK), sh.pad, s, \
                                                      a.ev0, a.ev1, 0, V, a.ld, a.scales, a.n,  \
                                                      a.j, a.w, ra, a.st, a.gated,              \
-                                                     a.with_norms)))                           \
+                                                     a.with_norms, sh.chunk)))                    \
     } else {                                                                                   \
-        CBG_FMT_SWITCH(a.fmt, (k_multidot<F, G><<<g, BLK, 0, s>>>(V, a.ld, a.scales, a.n, a.j,  \
+        CBG_FMT_SWITCH(a.fmt, (k_multidot<F, G><<<g, BLK, sh.pad, s>>>(V, a.ld, a.scales, a.n, a.j,  \
                                                                    a.w, ra, a.st, a.gated,     \
-                                                                   a.with_norms)))             \
+                                                                   a.with_norms, sh.chunk)))      \
     }
     if (a.gram) {
         CBG_MD(true)
@@ -2908,17 +3043,24 @@ void launch_update(const OrthArgs &a, hipStream_t s)
     StepArrays sa{};
     if (a.sa)
         sa = *(const StepArrays *)a.sa;
-#define CBG_UPD(R)                                                                            \
+#define CBG_UPDL(R, D)                                                                        \
     if (a.ev0) {                                                                              \
-        CBG_FMT_SWITCH(a.fmt, (hipExtLaunchKernelGGL(k_update<F, R>, dim3(g), dim3(BLK), 0, s, \
-                                                     a.ev0, a.ev1, 0, V, a.ld, a.scales, a.n, \
-                                                     a.j, a.coef, a.wio, a.dinv, ra, a.st,    \
-                                                     a.u, a.stw, a.G, sa, g0)))               \
+        CBG_FMT_SWITCH(a.fmt, (hipExtLaunchKernelGGL(k_update<F, R, D>, dim3(g), dim3(BLK), 0, \
+                                                     s, a.ev0, a.ev1, 0, V, a.ld, a.scales,   \
+                                                     a.n, a.j, a.coef, a.wio, a.dinv, ra,     \
+                                                     a.st, a.u, a.stw, a.G, sa, g0)))         \
     } else {                                                                                  \
-        CBG_FMT_SWITCH(a.fmt, (k_update<F, R><<<g, BLK, 0, s>>>(V, a.ld, a.scales, a.n, a.j,   \
-                                                                 a.coef, a.wio, a.dinv, ra,   \
-                                                                 a.st, a.u, a.stw, a.G, sa,   \
-                                                                 g0)))                        \
+        CBG_FMT_SWITCH(a.fmt, (k_update<F, R, D><<<g, BLK, 0, s>>>(V, a.ld, a.scales, a.n,    \
+                                                                    a.j, a.coef, a.wio,       \
+                                                                    a.dinv, ra, a.st, a.u,    \
+                                                                    a.stw, a.G, sa, g0)))     \
+    }
+    // deep rings below two tiles per CU (see k_update)
+#define CBG_UPD(R)                                                                            \
+    if (g0 < FULL_GRID) {                                                                     \
+        CBG_UPDL(R, true)                                                                     \
+    } else {                                                                                  \
+        CBG_UPDL(R, false)                                                                    \
     }
     switch (a.role) {
     case U_PLAIN: CBG_UPD(U_PLAIN) break;
@@ -2931,6 +3073,7 @@ void launch_update(const OrthArgs &a, hipStream_t s)
     default: CBG_UPD(U_COMBINE) break;
     }
 #undef CBG_UPD
+#undef CBG_UPDL
 }
 
 template <int F, int JM>

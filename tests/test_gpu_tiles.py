@@ -1,0 +1,48 @@
+"""The multi-dot and the update at the edges of their tiles and chunks.
+
+Rows: one below, at and one above whole tiles (2048 and 4096 rows), a single
+row, odd remainders.  Stored vectors: one, one more or less than a batch and
+than a ring of batches, and counts whose multi-dot splits into several
+chunks.  The entries of the basis beyond n (up to the leading dimension)
+hold all-ones codes, which decode to NaN in the float formats: a kernel that
+let them in would show it.  Compared with the oracle within the FP64 bounds
+of a dot and of an update, |err| <= c * terms * 2^-53 * sum|terms|.
+"""
+import numpy as np
+import pytest
+
+from tests.test_gpu_kernels import U, _basis
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+@pytest.mark.parametrize("fmt", ["fp64", "fp32", "fp16", "int16", "e4m3"])
+@pytest.mark.parametrize("n,j", [(1, 5), (2047, 3), (2049, 17), (4095, 9), (4096, 16), (4097, 8),
+                                 (12289, 33), (40961, 15)])
+def test_tile_edges(orc, dev, fmt, n, j):
+    import paper_2009_12101_amd as cbg
+    print(f"tile edges {fmt} n={n} j={j}", flush=True)
+    ld = (n + 15) // 16 * 16
+    raw, dec, scales = _basis(orc, fmt, n, j, ld, seed=n + j)
+    raw.view(np.uint8).reshape(j, -1)[:, n * raw.itemsize:] = 0xFF
+    w = np.random.default_rng(n).standard_normal(n)
+    Vd = torch.from_numpy(raw.view(np.uint8).reshape(-1)).to(dev)
+    sd = torch.from_numpy(scales).to(dev)
+    wd = torch.from_numpy(w).to(dev)
+    h = cbg.multidot(fmt, Vd, ld, sd, n, j, wd).cpu().numpy()
+    ho = dec @ w
+    assert np.all(np.abs(h - ho) <= 4 * n * U * (np.abs(dec) @ np.abs(w)) + 1e-300)
+    norms = cbg.update(fmt, Vd, ld, sd, n, j, torch.from_numpy(ho).to(dev), wd).cpu().numpy()
+    w2 = wd.cpu().numpy()
+    bound = 4 * (j + 1) * U * (np.abs(w) + np.abs(ho) @ np.abs(dec))
+    assert np.all(np.abs(w2 - (w - ho @ dec)) <= bound)
+    assert abs(norms[0] - np.linalg.norm(w2)) <= 1e-13 * norms[0]
+    assert norms[1] == np.abs(w2).max()
