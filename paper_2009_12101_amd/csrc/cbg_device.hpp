@@ -408,6 +408,10 @@ __device__ inline void block_sum_max(double &s, double &m)
 // ---------------------------------------------------------------------------
 // Device state of one solve (the scalars of Fig. 1 and the cycle flags).
 // ---------------------------------------------------------------------------
+// DevState::done: the cycle runs, has finished, or waits at a hard step for
+// the host to run that step's second pass
+enum { CYCLE_RUNS = 0, CYCLE_DONE = 1, CYCLE_PAUSED = 2 };
+
 struct DevState {
     // constants
     double nb;          // ||b||_2
@@ -422,14 +426,14 @@ struct DevState {
     int32_t breakdowns;
     int32_t nonfinite;  // a non-finite scalar appeared
     // current cycle
-    int32_t done;       // cycle finished: later step kernels do nothing
+    int32_t done;       // CYCLE_*: set, later step kernels do nothing
     int32_t jeff;       // steps taken in this cycle
     int32_t jprev;      // steps taken in the previous cycle
     int32_t reorth_all; // re-orthogonalise on every step (CGS2 ablation)
     int32_t reorth;     // the current step re-orthogonalises
     int32_t conv;       // recurrence residual met the tolerance
     int32_t hard;       // the current step took the explicit form (t1 << omega)
-    int32_t pad1;
+    uint32_t ticket;    // blocks of the one-pass update that have finished (see last_block)
     double beta;        // ||r||_2 at the cycle start
     double rmax;        // max |r_i| at the cycle start
     double omega;       // ||A M^-1 v||_2 (step 4)

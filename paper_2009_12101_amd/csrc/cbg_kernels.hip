@@ -154,46 +154,25 @@ __device__ double rotate_column(const double *c, int j, const double *__restrict
     return carry;
 }
 
-// Fig. 1 steps 9-12 and step 16, run by every thread of a one-block kernel.
+// Fig. 1 steps 9-12 and the new rotation of step 16, run by one thread.
 // Reading of step 12 (the literal test would end every re-orthogonalised
 // cycle): breakdown iff h_{j+1,j} = 0, or the second pass again lost more
-// than a factor eta.  The new column (h, plus u after a
-// re-orthogonalisation) meets the j-1 stored rotations (rotate_column), or,
-// with `rotated`, that was done already by the one-pass update's column
-// block (rows 0 .. j-2 in H, the carry in the state); thread 0 then forms
-// the new rotation and updates g.
-__device__ void finish_step(DevState *st, const StepArrays &a, int j, bool reorth, double t2,
-                            double wmax2, bool rotated = false)
+// than a factor eta.  t: h_{j+1,j}; t1: the norm before the second pass
+// (reorth); wmax: max|w|; carry: row j-1 of the new column after the stored
+// rotations.
+__device__ __forceinline__ void close_step(DevState *st, const StepArrays &a, int j, bool reorth,
+                                           bool hard, double t1, double t, double wmax,
+                                           double carry)
 {
-    __shared__ double lh[MAX_RESTART];
-    __shared__ double pa[2][MAX_RESTART], pb[2][MAX_RESTART];
-    const int tid = threadIdx.x;
     const int jc = j - 1;
     const int m = st->m;
     double *Hc = a.H + (size_t)jc * (m + 1);
-    double carry;
-    if (rotated) {
-        carry = st->carry;
-    } else {
-        for (int k = tid; k < j; k += blockDim.x)
-            lh[k] = reorth ? a.h[k] + a.u[k] : a.h[k];
-        __syncthreads();
-        carry = rotate_column(lh, j, a.cs, a.sn, Hc, pa, pb);
-    }
-    if (tid != 0)
-        return;
-    double t = st->t;
-    bool brk;
-    if (reorth) {
-        brk = (t2 == 0.0) || (t2 < st->eta * t);
-        t = t2;
-        st->wmax = wmax2;
+    const bool brk = t == 0.0 || (reorth && t < st->eta * t1);
+    if (reorth)
         st->reorths += 1;
-    } else {
-        brk = (t == 0.0);
-    }
+    st->wmax = wmax;
     st->t = t;
-    const double rr = sqrt(carry * carry + t * t);
+    const double rr = sqrt(fma(carry, carry, t * t));
     double c = 1.0, sn = 0.0;
     if (rr > 0.0) {
         c = carry / rr;
@@ -215,7 +194,7 @@ __device__ void finish_step(DevState *st, const StepArrays &a, int j, bool reort
     const bool conv = fabs(gnew) <= st->tau_nb;
     if (brk)
         st->breakdowns += 1;
-    a.flags[jc] = (reorth ? 1 : 0) | (brk ? 2 : 0) | (st->hard ? 4 : 0);
+    a.flags[jc] = (reorth ? 1 : 0) | (brk ? 2 : 0) | (hard ? 4 : 0);
     st->jeff = j;
     if (!finite)
         st->nonfinite = 1;
@@ -223,8 +202,34 @@ __device__ void finish_step(DevState *st, const StepArrays &a, int j, bool reort
         st->done = 1;
         st->conv = conv ? 1 : 0;
     } else {
-        a.scales[j] = make_param(st->fmt, st->wmax / t).scale;
+        a.scales[j] = make_param(st->fmt, wmax / t).scale;
     }
+}
+
+// The end of a step, run by every thread of a one-block kernel.  The new
+// column (h, plus u after a re-orthogonalisation) meets the j-1 stored
+// rotations (rotate_column), or, with `rotated`, that was done already by
+// the one-pass update's column block (rows 0 .. j-2 in H, the carry in the
+// state); thread 0 then closes the step.  Without reorth the state holds the
+// step's t and max|w|; with it, t1, and t2 and wmax2 are the second pass's.
+__device__ void finish_step(DevState *st, const StepArrays &a, int j, bool reorth, double t2,
+                            double wmax2, bool rotated = false)
+{
+    __shared__ double lh[MAX_RESTART];
+    __shared__ double pa[2][MAX_RESTART], pb[2][MAX_RESTART];
+    const int tid = threadIdx.x;
+    double carry;
+    if (rotated) {
+        carry = st->carry;
+    } else {
+        for (int k = tid; k < j; k += blockDim.x)
+            lh[k] = reorth ? a.h[k] + a.u[k] : a.h[k];
+        __syncthreads();
+        carry = rotate_column(lh, j, a.cs, a.sn, a.H + (size_t)(j - 1) * (st->m + 1), pa, pb);
+    }
+    if (tid == 0)
+        close_step(st, a, j, reorth, st->hard != 0, st->t, reorth ? t2 : st->t,
+                   reorth ? wmax2 : st->wmax, carry);
 }
 
 // ---------------------------------------------------------------------------
@@ -370,7 +375,8 @@ enum {
 };
 // roles: SR_NONE no partials (skipped once the cycle is done); SR_STEP
 // partials of ||y||^2 and max|y_i| (skipped once done); SR_FREE partials,
-// never skipped (explicit residual, kernel-level calls).
+// skipped in a paused cycle only (explicit residual) or never (kernel-level
+// calls).
 enum { SR_NONE = 0, SR_STEP = 1, SR_FREE = 2 };
 
 constexpr bool sp_step(int mode) { return (mode & 8) != 0; }
@@ -446,7 +452,7 @@ __global__ __launch_bounds__(BLK) void k_spmv(int n, int64_t ldy, const int32_t 
                                               const DevState *st, uint8_t *__restrict__ Q,
                                               const double *__restrict__ qscale, int fmt)
 {
-    if (st && role != SR_FREE && st->done)
+    if (st && (role != SR_FREE ? st->done : st->done == CYCLE_PAUSED))
         return;
     double tdiv = 1.0;
     EncParam ep{1.0, 0};
@@ -578,7 +584,7 @@ __global__ __launch_bounds__(BLK) void k_spmv_rp(int n, int64_t ldy,
     constexpr int NPART = BLK / RPB;
     constexpr int UNR = 4;
     constexpr bool FLT = (MODE & 7) == SP_FLOATVAL || (MODE & 7) == SP_ACCUM;
-    if (st && role != SR_FREE && st->done)
+    if (st && (role != SR_FREE ? st->done : st->done == CYCLE_PAUSED))
         return;
     double tdiv = 1.0;
     EncParam ep{1.0, 0};
@@ -732,7 +738,7 @@ __global__ __launch_bounds__(BLK) void k_spmv_sell(
     const double *__restrict__ qscale, int fmt)
 {
 #pragma clang fp contract(off)
-    if (st && role != SR_FREE && st->done)
+    if (st && (role != SR_FREE ? st->done : st->done == CYCLE_PAUSED))
         return;
     // DIX: columns as row + offset, the offset's index one byte per entry
     __shared__ int32_t ldg[DIX ? SELL_MAX_DIAG : 1];
@@ -1257,8 +1263,42 @@ __global__ __launch_bounds__(BLK) CBG_MD_ATTR void k_multidot(const uint8_t *__r
 constexpr int RBLK = 256;
 constexpr int RWAVES = RBLK / 64;
 
+// Values that blocks of one launch pass to its last block: written through
+// to, and read from, the level that all XCDs share (each has an L2 of its
+// own, coherent only at kernel boundaries).
+__device__ __forceinline__ void shared_store(double *p, double v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double shared_load(const double *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Counts the calling blocks of a launch; true in the block that arrives
+// last, when every other block's shared_stores have completed (each waits
+// for its own before it counts).  Block-uniform call; the stores before it
+// come from thread 0.  The last block leaves the counter at 0 for the next
+// launch.
+__device__ bool last_block(uint32_t *ticket, uint32_t blocks)
+{
+    __shared__ int last;
+    if (threadIdx.x == 0) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const uint32_t at =
+            __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last = at == blocks - 1;
+        if (last)
+            __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    return last != 0;
+}
+
 // One wave folds block partials src[0 .. nb) (16 independent loads in flight
 // per lane, fixed order); every lane returns the total.  nb = 0 gives 0.
+// SHARED: partials of the same launch.
+template <bool SHARED = false>
 __device__ __forceinline__ double wave_fold(const double *__restrict__ src, int nb, bool is_max)
 {
     constexpr int U = 16;
@@ -1271,7 +1311,8 @@ __device__ __forceinline__ double wave_fold(const double *__restrict__ src, int 
         double x[U];
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            x[u] = src[min(b0 + 64 * u, nb - 1)];
+            x[u] = SHARED ? shared_load(src + min(b0 + 64 * u, nb - 1))
+                          : src[min(b0 + 64 * u, nb - 1)];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const double xv = (b0 + 64 * u < nb) ? x[u] : 0.0;
@@ -1289,13 +1330,14 @@ __device__ __forceinline__ double wave_fold(const double *__restrict__ src, int 
 // starting at w * ceil(nb / 4), and the four wave totals are combined in
 // wave order (so the result depends on nb only, not on timing).  Every
 // thread returns the total; block-uniform call.
+template <bool SHARED = false>
 __device__ double block_fold(const double *__restrict__ src, int nb, bool is_max)
 {
     __shared__ double part[RWAVES];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int q = (nb + RWAVES - 1) / RWAVES;
     const int lo = min(wave * q, nb), hi = min(lo + q, nb);
-    const double a = wave_fold(src + lo, hi - lo, is_max);
+    const double a = wave_fold<SHARED>(src + lo, hi - lo, is_max);
     if (lane == 0)
         part[wave] = a;
     __syncthreads();
@@ -1393,7 +1435,7 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
                                                 const DevState *st,
                                                 double *__restrict__ uio, DevState *stw,
                                                 const double *__restrict__ G, StepArrays sa,
-                                                int nb_first)
+                                                int nb_first, int close)
 {
     int j = j_arg;
     if constexpr (ROLE == U_STEP1 || ROLE == U_STEP2 || ROLE == U_STEP1N || ROLE == U_CGS2 ||
@@ -1405,8 +1447,12 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
         if (ROLE == U_HARD && !st->hard)
             return;
     }
-    if constexpr (ROLE == U_SOLUTION || ROLE == U_COMBINE)
-        j = st->jeff;
+    if constexpr (ROLE == U_SOLUTION || ROLE == U_COMBINE) {
+        // a cycle paused at a hard step has no solution yet: x += M^-1 0
+        j = st->done == CYCLE_PAUSED ? 0 : st->jeff;
+        if (ROLE == U_SOLUTION && j == 0)
+            return;
+    }
     using T = Fmt<F>;
     using Tile = VecTile<F>;
     constexpr int VW = T::VW, CH = T::CH, UNR = DEEP ? 4 / CH : CH == 1 ? 2 : 1;
@@ -1453,22 +1499,46 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
         double(*pb)[MAX_RESTART] = (double(*)[MAX_RESTART])(lp + 2 * MAX_RESTART);
         const double carry = rotate_column(c, j, sa.cs, sa.sn, Hc, pa, pb);
         if (tid == 0)
-            stw->carry = carry;
+            shared_store(&stw->carry, carry);
     };
     if ((int)blockIdx.x < ntb && blockIdx.x < ntiles)
         start_tile(blockIdx.x);
     if constexpr (T::SCALED)
         for (int k = tid; k < j + UNR; k += BLK)
             lsc[k] = k < j ? scales[k] : 1.0;
-    bool hard = false;
+    bool hard = false, ro = false;
+    double t1 = 0.0;
+    // U_CGS2 with `close`: the block that finishes last folds the norms (in
+    // the order of the closing fold) and closes the step, which saves that
+    // launch and the second pass's (5.4 and 4.5 us of a step) on every step
+    // that is not hard; a hard step pauses the cycle for the host, which runs
+    // the second pass and the close as launches of their own.
+    auto close_cycle_step = [&]() {
+        if (!last_block(&stw->ticket, gridDim.x))
+            return;
+        if (hard) {
+            if (tid == 0) {
+                stw->hard = 1;
+                stw->done = CYCLE_PAUSED;
+            }
+            return;
+        }
+        const double a0 = block_fold<true>(ra.part, ntb, false);
+        const double a1 = block_fold<true>(ra.part + ra.stride, ntb, true);
+        if (tid == 0) {
+            stw->hard = 0;
+            stw->reorth = ro ? 1 : 0;
+            close_step(stw, sa, j, ro, false, t1, sqrt(a0), a1, shared_load(&stw->carry));
+        }
+    };
     if constexpr (ROLE == U_CGS2) {
         // Every block forms the same u = h - G h (G symmetric: wave wv sums
         // G[l][k] h_l over its quarter of l for k = lane, lane + 64, ...,
         // reading rows of G, contiguous in k), then the same t1^2 =
         // ||w - V h||^2 = omega^2 - h^T h - h^T u, decides step 7, and updates
-        // with h + u (re-orthogonalising) or h.  Block 0 publishes u, the
-        // decision and t1 for the closing fold.  A hard step updates with h
-        // only and adds the explicit re-dot of the result.
+        // with h + u (re-orthogonalising) or h.  Without `close`, block 0
+        // publishes the decision and t1 for the closing fold.  A hard step
+        // updates with h only and adds the explicit re-dot of the result.
         for (int k = tid; k < j; k += BLK)
             lh[k] = coef[k];
         __syncthreads();
@@ -1515,15 +1585,11 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
         const double omega = st->omega;
         const double t1sq = omega * omega - hh - hu;
         hard = !(t1sq >= HARD_RATIO * omega * omega);       // also when not finite
-        const double t1 = hard ? 0.0 : sqrt(t1sq);
-        const bool ro = !hard && (st->reorth_all || t1 < st->eta * omega);
-        for (int k = tid; k < j; k += BLK) {
-            const double uk = lc[k];
-            if (blockIdx.x == 0)
-                uio[k] = uk;
-            lc[k] = ro ? lh[k] + uk : lh[k];
-        }
-        if (blockIdx.x == 0 && tid == 0) {
+        t1 = hard ? 0.0 : sqrt(t1sq);
+        ro = !hard && (st->reorth_all || t1 < st->eta * omega);
+        for (int k = tid; k < j; k += BLK)
+            lc[k] = ro ? lh[k] + lc[k] : lh[k];
+        if (!close && blockIdx.x == 0 && tid == 0) {
             stw->hard = hard ? 1 : 0;
             if (!hard) {
                 stw->reorth = ro ? 1 : 0;
@@ -1536,6 +1602,8 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
                 __syncthreads();                // lc complete
                 rotate(lc);
             }
+            if (close)
+                close_cycle_step();
             return;
         }
         if (hard) {
@@ -1562,8 +1630,8 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
                 lr[0][wv] = a;
         }
         __syncthreads();
-        const double t1 = sqrt(lr[0][0]);
-        const bool ro = st->reorth_all || t1 < st->eta * st->omega;
+        t1 = sqrt(lr[0][0]);
+        ro = st->reorth_all || t1 < st->eta * st->omega;
         if (blockIdx.x == 0) {
             for (int k = tid; k < j; k += BLK)
                 uio[k] = lc[k];
@@ -1720,9 +1788,12 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
         row = j + 2;
     block_sum_max(ssq, mx);
     if (threadIdx.x == 0) {
-        ra.part[(size_t)row * ra.stride + blockIdx.x] = ssq;
-        ra.part[(size_t)(row + 1) * ra.stride + blockIdx.x] = mx;
+        shared_store(ra.part + (size_t)row * ra.stride + blockIdx.x, ssq);
+        shared_store(ra.part + (size_t)(row + 1) * ra.stride + blockIdx.x, mx);
     }
+    if constexpr (ROLE == U_CGS2)
+        if (close)
+            close_cycle_step();
 }
 
 // ---------------------------------------------------------------------------
@@ -2231,6 +2302,8 @@ __global__ __launch_bounds__(RBLK) void k_reduce(RedWs ws, int role, int nb_orth
         if ((role == RR_T2 || role == RR_MGS_U) && !st->reorth)
             return;
     }
+    if (role == RR_RESID && st->done == CYCLE_PAUSED)
+        return;
     if (role == RR_MGS_H || role == RR_MGS_U) {       // one value, one block
         const double a = block_fold(ws.orth, nb_orth, false);
         if (threadIdx.x == 0)
@@ -3048,12 +3121,14 @@ void launch_update(const OrthArgs &a, hipStream_t s)
         CBG_FMT_SWITCH(a.fmt, (hipExtLaunchKernelGGL(k_update<F, R, D>, dim3(g), dim3(BLK), 0, \
                                                      s, a.ev0, a.ev1, 0, V, a.ld, a.scales,   \
                                                      a.n, a.j, a.coef, a.wio, a.dinv, ra,     \
-                                                     a.st, a.u, a.stw, a.G, sa, g0)))         \
+                                                     a.st, a.u, a.stw, a.G, sa, g0,           \
+                                                     a.close)))                               \
     } else {                                                                                  \
         CBG_FMT_SWITCH(a.fmt, (k_update<F, R, D><<<g, BLK, 0, s>>>(V, a.ld, a.scales, a.n,    \
                                                                     a.j, a.coef, a.wio,       \
                                                                     a.dinv, ra, a.st, a.u,    \
-                                                                    a.stw, a.G, sa, g0)))     \
+                                                                    a.stw, a.G, sa, g0,       \
+                                                                    a.close)))                \
     }
     // deep rings below two tiles per CU (see k_update)
 #define CBG_UPD(R)                                                                            \
@@ -3268,6 +3343,15 @@ void launch_clear_flags(DevState *st, unsigned *bad, hipStream_t s)
 {
     k_clear_flags<<<1, 64, 0, s>>>(st, bad);
 }
+
+// A cycle paused at a hard step goes on with that step's second pass.
+__global__ void k_resume(DevState *st)
+{
+    if (threadIdx.x == 0)
+        st->done = 0;
+}
+
+void launch_resume(DevState *st, hipStream_t s) { k_resume<<<1, 64, 0, s>>>(st); }
 
 // p[0 .. count) = 0 with a kernel (no memset node where a caller captures)
 __global__ void k_fill_zero(double *p, int count)

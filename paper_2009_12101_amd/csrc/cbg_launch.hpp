@@ -58,6 +58,7 @@ struct OrthArgs {
     DevState *stw;        // one-pass update: the step-7 decision and t1
     const double *G;      // one-pass update: the Gram matrix of the stored basis
     const void *sa;       // one-pass update: the step arrays (H, cs, sn) of the column block
+    int close;            // one-pass update: its last block closes the step
     const double *coef;   // update coefficients
     double *wio;          // update: the vector updated in place (or written)
     const double *dinv;
@@ -148,6 +149,7 @@ void launch_init_state(DevState *st, int n, int m, int fmt, double tol, double e
 // copy with diagonal indices when `a` carries one (set_matrix), else from CSR
 void launch_jacobi_setup(const SpmvArgs &a, int64_t ld, double *dinv, unsigned *bad,
                          hipStream_t s);
+void launch_resume(DevState *st, hipStream_t s);
 void launch_clear_flags(DevState *st, unsigned *bad, hipStream_t s);
 void launch_fill_zero(double *p, int count, hipStream_t s);
 void launch_backsolve(const DevState *st, const void *sa, hipStream_t s);

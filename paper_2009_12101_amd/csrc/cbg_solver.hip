@@ -526,6 +526,17 @@ int cbgmres_solve(const cbg_csr *A, const double *b, double *x, const cbg_opts *
     bool prev_cycle = false;
     int prev_pc = pc;
 
+    bool pause_hard = true;             // the update closes its step; a hard one pauses the cycle
+    // the one-pass form's explicit second pass (nothing unless the step is
+    // hard) and the close
+    auto second_pass = [&](int j, double *w) {
+        OrthArgs o{};
+        o.fmt = fmt; o.V = W.V; o.ld = ld; o.scales = W.scales; o.n = n; o.j = j;
+        o.wio = w; o.ws = W.red; o.st = W.st; o.coef = W.h; o.role = 7 /*U_HARD*/;
+        o.u = W.u; o.stw = W.st; o.G = W.G; o.sa = sa;
+        launch_update(o, s);
+        launch_reduce(W.red, RR_C2, nb_orth, 0, j, W.st, sa, nullptr, fmt, s);
+    };
     for (;;) {
         // Fig. 1 step 1 / step 18: explicit residual r = b - A x into w,
         // ||r|| and max|r_i|; resets the cycle state.
@@ -548,138 +559,154 @@ int cbgmres_solve(const cbg_csr *A, const double *b, double *x, const cbg_opts *
         }
         HIP_TRY(hipStreamSynchronize(s));
 
-        if (prev_cycle) {
-            // account for the cycle that just ended
-            const int jeff = hs.jprev;
-            if (prof) {
-                // every launch of the cycle is timed, including the ones that
-                // found the cycle finished (they move no bytes)
-                for (int j = 1; j <= jl; ++j) {
-                    if (!ev_on[j])
-                        continue;
-                    const bool ro = j <= jeff && (cyc_flags[j - 1] & 1);
-                    for (int k = 0; k < 4; ++k) {
-                        if ((k == 2 && (fused(j) || gram)) || (k == 3 && onepass) ||
-                            !profiled(k))
-                            continue;            // no separate re-dot launch, or not timed
-                        float ms;
-                        HIP_TRY(hipEventElapsedTime(&ms, evs.at(j, k, 0), evs.at(j, k, 1)));
-                        const bool work = j <= jeff && (k < 3 || ro);
-                        const double by = !work ? 0.0
-                                          : k == 0 && gram ? bm.dot(j) + n * bm.bs
-                                          : (k % 2 == 0) ? bm.dot(j) : bm.upd(j);
-                        res->prof_orth_ms += ms;
-                        res->prof_orth_bytes += by;
-                        res->prof_orth_launches += 1;
-                        if (k % 2 == 0) {
-                            res->prof_dot_ms += ms;
-                            res->prof_dot_bytes += by;
-                            res->prof_dot_launches += 1;
-                        } else if (k == 1 && fused(j)) {
-                            res->prof_fused_ms += ms;
-                            res->prof_fused_bytes += by;
-                            res->prof_fused_launches += 1;
+        int j0 = 1;                     // first step to enqueue
+        if (hs.done == CYCLE_PAUSED) {
+            // The step after the jeff finished ones is hard: its second pass
+            // and close, then the rest of the cycle.  (What was enqueued behind
+            // the pause, the residual above included, did nothing.)  A system
+            // with one hard step tends to have more: from here on every step
+            // carries its second pass, as launches that return at once unless
+            // it is hard.
+            pause_hard = false;
+            model_bytes -= bm.spmv() + 8.0 * n;
+            j0 = hs.jeff + 1;
+            launch_resume(W.st, s);
+            second_pass(j0, j0 % 2 ? W.w1 : W.w0);
+            j0 += 1;
+        } else {
+            if (prev_cycle) {
+                // account for the cycle that just ended
+                const int jeff = hs.jprev;
+                if (prof) {
+                    // every launch of the cycle is timed, including the ones that
+                    // found the cycle finished (they move no bytes)
+                    for (int j = 1; j <= jl; ++j) {
+                        if (!ev_on[j])
+                            continue;
+                        const bool ro = j <= jeff && (cyc_flags[j - 1] & 1);
+                        for (int k = 0; k < 4; ++k) {
+                            if ((k == 2 && (fused(j) || gram)) || (k == 3 && onepass) ||
+                                !profiled(k))
+                                continue;            // no separate re-dot launch, or not timed
+                            float ms;
+                            HIP_TRY(hipEventElapsedTime(&ms, evs.at(j, k, 0), evs.at(j, k, 1)));
+                            const bool work = j <= jeff && (k < 3 || ro);
+                            const double by = !work ? 0.0
+                                              : k == 0 && gram ? bm.dot(j) + n * bm.bs
+                                              : (k % 2 == 0) ? bm.dot(j) : bm.upd(j);
+                            res->prof_orth_ms += ms;
+                            res->prof_orth_bytes += by;
+                            res->prof_orth_launches += 1;
+                            if (k % 2 == 0) {
+                                res->prof_dot_ms += ms;
+                                res->prof_dot_bytes += by;
+                                res->prof_dot_launches += 1;
+                            } else if (k == 1 && fused(j)) {
+                                res->prof_fused_ms += ms;
+                                res->prof_fused_bytes += by;
+                                res->prof_fused_launches += 1;
+                            }
                         }
                     }
                 }
+                if (prof_spmv) {
+                    // the step SpMV: the plain product when a pass formed M^-1 v,
+                    // else the gather variant, which also stores v_j
+                    const bool gather = !norm_pass && prev_pc != CBG_PC_STENCIL &&
+                                        prev_pc != CBG_PC_SPARSE && prev_pc != CBG_PC_BLOCK_JACOBI;
+                    for (int j = 1; j <= jl; ++j) {
+                        if (!ev_on[j])
+                            continue;
+                        float ms;
+                        HIP_TRY(hipEventElapsedTime(&ms, evs.at(j, 4, 0), evs.at(j, 4, 1)));
+                        res->prof_spmv_ms += ms;
+                        res->prof_spmv_bytes +=
+                            j <= jeff ? (gather ? bm.spmv_step() : bm.spmv()) : 0.0;
+                        res->prof_spmv_launches += 1;
+                    }
+                }
+                for (int j = 1; j <= jeff; ++j) {
+                    const bool ro = cyc_flags[j - 1] & 1;
+                    if (cyc_flags[j - 1] & 4)
+                        res->explicit_steps += 1;
+                    if (hist_n < hist_len)
+                        hist_out[hist_n] = cyc_hist[j - 1];
+                    ++hist_n;
+                    // MGS pass: w read j + 1 times and written j times, each
+                    // stored vector read twice
+                    const double b_mgs = 2.0 * j * n * bm.bs + (2.0 * j + 1.0) * 8.0 * n;
+                    double b_step = bm.spmv_step() + (mgs ? b_mgs : bm.dot(j) + bm.upd(j));
+                    if (prev_pc == CBG_PC_JACOBI) b_step += 8.0 * n;
+                    if (prev_pc == CBG_PC_SPARSE) b_step += 8.0 * A->nnz + 4.0 * (n + 1) + 16.0 * n;
+                    // the stencil pass in place of the normalising one: codes
+                    // (27 x 2 bytes), dinv, and z written and read
+                    if (prev_pc == CBG_PC_STENCIL) b_step += 62.0 * n + 16.0 * n;
+                    if (prev_pc == CBG_PC_BLOCK_JACOBI) b_step += bj_bytes + 16.0 * n;
+                    if (norm_pass && prev_pc != CBG_PC_STENCIL)
+                        b_step += 16.0 * n;  // v written by the pass, read by the SpMV
+                    if (!fused(j) && !mgs && !gram)
+                        b_step += bm.dot(j);             // the separate re-dot pass
+                    if (gram)
+                        b_step += n * bm.bs;             // the newest vector's tile for G
+                    if (ro && !onepass) b_step += mgs ? b_mgs : bm.upd(j);
+                    // a hard step of the one-pass form: the re-dot pass, and the
+                    // second update if it re-orthogonalised
+                    if (onepass && (cyc_flags[j - 1] & 4))
+                        b_step += j * n * bm.bs + (ro ? bm.upd(j) : 0.0);
+                    model_bytes += b_step;
+                }
+                model_bytes += jeff * n * bm.bs + 16.0 * n;     // solution update
             }
-            if (prof_spmv) {
-                // the step SpMV: the plain product when a pass formed M^-1 v,
-                // else the gather variant, which also stores v_j
-                const bool gather = !norm_pass && prev_pc != CBG_PC_STENCIL &&
-                                    prev_pc != CBG_PC_SPARSE && prev_pc != CBG_PC_BLOCK_JACOBI;
-                for (int j = 1; j <= jl; ++j) {
-                    if (!ev_on[j])
-                        continue;
-                    float ms;
-                    HIP_TRY(hipEventElapsedTime(&ms, evs.at(j, 4, 0), evs.at(j, 4, 1)));
-                    res->prof_spmv_ms += ms;
-                    res->prof_spmv_bytes +=
-                        j <= jeff ? (gather ? bm.spmv_step() : bm.spmv()) : 0.0;
-                    res->prof_spmv_launches += 1;
+
+            rho = hs.beta;
+            if (hs.nonfinite || !isfinite(rho)) {
+                if (droppable(pc) && opt->fallback && cycles > 0) {
+                    // plain CB-GMRES takes over from the last finite iterate
+                    HIP_TRY(hipMemcpyAsync(x, W.xprev, (size_t)n * sizeof(double),
+                                           hipMemcpyDeviceToDevice, s));
+                    pc = CBG_PC_NONE;
+                    res->fell_back = 1;
+                    stagnant = 0;
+                    rho_prev = INFINITY;
+                    prev_cycle = false;
+                    launch_clear_flags(W.st, nullptr, s);
+                    continue;
+                }
+                status = CBG_E_NONFINITE;
+                break;
+            }
+            if (rho <= hs.tau_nb) {
+                status = CBG_OK;
+                break;
+            }
+            if (hs.it >= opt->maxiter) {
+                status = CBG_NOT_CONVERGED;
+                break;
+            }
+            if (droppable(pc) && opt->fallback) {
+                stagnant = rho > 0.99 * rho_prev ? stagnant + 1 : 0;
+                if (stagnant >= 2) {
+                    pc = CBG_PC_NONE;
+                    res->fell_back = 1;
+                    stagnant = 0;
                 }
             }
-            for (int j = 1; j <= jeff; ++j) {
-                const bool ro = cyc_flags[j - 1] & 1;
-                if (cyc_flags[j - 1] & 4)
-                    res->explicit_steps += 1;
-                if (hist_n < hist_len)
-                    hist_out[hist_n] = cyc_hist[j - 1];
-                ++hist_n;
-                // MGS pass: w read j + 1 times and written j times, each
-                // stored vector read twice
-                const double b_mgs = 2.0 * j * n * bm.bs + (2.0 * j + 1.0) * 8.0 * n;
-                double b_step = bm.spmv_step() + (mgs ? b_mgs : bm.dot(j) + bm.upd(j));
-                if (prev_pc == CBG_PC_JACOBI) b_step += 8.0 * n;
-                if (prev_pc == CBG_PC_SPARSE) b_step += 8.0 * A->nnz + 4.0 * (n + 1) + 16.0 * n;
-                // the stencil pass in place of the normalising one: codes
-                // (27 x 2 bytes), dinv, and z written and read
-                if (prev_pc == CBG_PC_STENCIL) b_step += 62.0 * n + 16.0 * n;
-                if (prev_pc == CBG_PC_BLOCK_JACOBI) b_step += bj_bytes + 16.0 * n;
-                if (norm_pass && prev_pc != CBG_PC_STENCIL)
-                    b_step += 16.0 * n;  // v written by the pass, read by the SpMV
-                if (!fused(j) && !mgs && !gram)
-                    b_step += bm.dot(j);             // the separate re-dot pass
-                if (gram)
-                    b_step += n * bm.bs;             // the newest vector's tile for G
-                if (ro && !onepass) b_step += mgs ? b_mgs : bm.upd(j);
-                // a hard step of the one-pass form: the re-dot pass, and the
-                // second update if it re-orthogonalised
-                if (onepass && (cyc_flags[j - 1] & 4))
-                    b_step += j * n * bm.bs + (ro ? bm.upd(j) : 0.0);
-                model_bytes += b_step;
-            }
-            model_bytes += jeff * n * bm.bs + 16.0 * n;     // solution update
-        }
-
-        rho = hs.beta;
-        if (hs.nonfinite || !isfinite(rho)) {
-            if (droppable(pc) && opt->fallback && cycles > 0) {
-                // plain CB-GMRES takes over from the last finite iterate
-                HIP_TRY(hipMemcpyAsync(x, W.xprev, (size_t)n * sizeof(double),
+            rho_prev = rho;
+            if (droppable(pc) && opt->fallback)
+                HIP_TRY(hipMemcpyAsync(W.xprev, x, (size_t)n * sizeof(double),
                                        hipMemcpyDeviceToDevice, s));
-                pc = CBG_PC_NONE;
-                res->fell_back = 1;
-                stagnant = 0;
-                rho_prev = INFINITY;
-                prev_cycle = false;
-                launch_clear_flags(W.st, nullptr, s);
-                continue;
-            }
-            status = CBG_E_NONFINITE;
-            break;
+            cycles += 1;
+            prev_cycle = true;
+            prev_pc = pc;
         }
-        if (rho <= hs.tau_nb) {
-            status = CBG_OK;
-            break;
-        }
-        if (hs.it >= opt->maxiter) {
-            status = CBG_NOT_CONVERGED;
-            break;
-        }
-        if (droppable(pc) && opt->fallback) {
-            stagnant = rho > 0.99 * rho_prev ? stagnant + 1 : 0;
-            if (stagnant >= 2) {
-                pc = CBG_PC_NONE;
-                res->fell_back = 1;
-                stagnant = 0;
-            }
-        }
-        rho_prev = rho;
-        if (droppable(pc) && opt->fallback)
-            HIP_TRY(hipMemcpyAsync(W.xprev, x, (size_t)n * sizeof(double),
-                                   hipMemcpyDeviceToDevice, s));
-        cycles += 1;
-        prev_cycle = true;
-        prev_pc = pc;
 
         // The residual r sits in w0 with t = beta; step 1's SpMV forms
         // v_1 = r / beta and stores it as basis vector 1.
-        double *cur = W.w0, *nxt = W.w1;
+        double *cur = j0 % 2 ? W.w0 : W.w1, *nxt = j0 % 2 ? W.w1 : W.w0;
         watch.reset();
         jl = m;
-        for (int j = 1; j <= m; ++j) {
-            if (j > 1 && (j - 1) % STEP_CHUNK == 0) {
+        for (int j = j0; j <= m; ++j) {
+            if (j > j0 && (j - 1) % STEP_CHUNK == 0) {
                 const int w = watch.boundary((j - 1) / STEP_CHUNK, &W.st->done, s);
                 if (w < 0)
                     return fail(CBG_E_HIP);
@@ -790,15 +817,14 @@ int cbgmres_solve(const cbg_csr *A, const double *b, double *x, const cbg_opts *
             o.coef = W.h; o.role = 1 /*U_STEP1*/;
             timed(1);
             if (onepass) {
-                // u = h - G h and steps 5-10 in one update with h + u or h;
-                // a hard step's explicit second pass (nothing otherwise);
-                // the close
+                // u = h - G h, steps 5-10 in one update with h + u or h, and
+                // the close; a hard step pauses the cycle, or (once one was
+                // met) takes its second pass and the close here
                 o.role = 6 /*U_CGS2*/; o.u = W.u; o.stw = W.st; o.G = W.G; o.sa = sa;
+                o.close = pause_hard ? 1 : 0;
                 launch_update(o, s);
-                o.role = 7 /*U_HARD*/;
-                o.ev0 = o.ev1 = nullptr;        // the events belong to the update above
-                launch_update(o, s);
-                launch_reduce(W.red, RR_C2, nb_orth, 0, j, W.st, sa, nullptr, fmt, s);
+                if (!pause_hard)
+                    second_pass(j, nxt);
                 double *t = cur;
                 cur = nxt;
                 nxt = t;
