@@ -183,7 +183,9 @@ typedef struct {
  * entry by t (one division per nonzero instead of per row) and with Jacobi
  * reads D^-1 per nonzero.
  * Neither bit: the pass when the mean row length exceeds 12 nonzeros or the
- * preconditioner is Jacobi, the gather otherwise.  Both bits: argument
+ * preconditioner is Jacobi, the gather otherwise (up to 65536 rows the pass's
+ * work runs in the gather too, which saves its launch; model_bytes counts
+ * the pass).  Both bits: argument
  * error.  SPMV_VHAT and the block-Jacobi preconditioner always take their
  * own paths. */
 #define CBG_FLAG_NORMALISE_PASS 64

@@ -160,19 +160,35 @@ __device__ double rotate_column(const double *c, int j, const double *__restrict
 // than a factor eta.  t: h_{j+1,j}; t1: the norm before the second pass
 // (reorth); wmax: max|w|; carry: row j-1 of the new column after the stored
 // rotations.
-__device__ __forceinline__ void close_step(DevState *st, const StepArrays &a, int j, bool reorth,
-                                           bool hard, double t1, double t, double wmax,
-                                           double carry)
+//
+// What it reads of the state comes in a CloseIn, which the one-pass update
+// loads at its start: the update's last block would otherwise wait for it at
+// the very end of the step.
+struct CloseIn {
+    double eta, nb, tau_nb, gj;
+    int64_t it, maxiter, reorths;
+    int32_t m, fmt, breakdowns;
+};
+__device__ __forceinline__ CloseIn load_close(const DevState *st, const StepArrays &a, int j)
+{
+    return {st->eta,     st->nb,      st->tau_nb, a.g[j - 1], st->it,
+            st->maxiter, st->reorths, st->m,      st->fmt,    st->breakdowns};
+}
+
+__device__ __forceinline__ void close_step(DevState *st, const StepArrays &a, const CloseIn &in,
+                                           int j, bool reorth, bool hard, double omega, double t1,
+                                           double t, double wmax, double carry)
 {
     const int jc = j - 1;
-    const int m = st->m;
-    double *Hc = a.H + (size_t)jc * (m + 1);
-    const bool brk = t == 0.0 || (reorth && t < st->eta * t1);
+    double *Hc = a.H + (size_t)jc * (in.m + 1);
+    const bool brk = t == 0.0 || (reorth && t < in.eta * t1);
     if (reorth)
-        st->reorths += 1;
+        st->reorths = in.reorths + 1;
     st->wmax = wmax;
     st->t = t;
-    const double rr = sqrt(fma(carry, carry, t * t));
+    // contraction written out: the rounding must not depend on where the
+    // compiler inlines this
+    const double rr = sqrt(reorth ? fma(t, t, carry * carry) : fma(carry, carry, t * t));
     double c = 1.0, sn = 0.0;
     if (rr > 0.0) {
         c = carry / rr;
@@ -182,27 +198,26 @@ __device__ __forceinline__ void close_step(DevState *st, const StepArrays &a, in
     a.sn[jc] = sn;
     Hc[jc] = rr;
     Hc[j] = 0.0;
-    const double gj = a.g[jc];
-    const double gnew = -sn * gj;
+    const double gnew = -sn * in.gj;
     a.g[j] = gnew;
-    a.g[jc] = c * gj;
-    st->it += 1;
-    const double rec = fabs(gnew) / st->nb;
+    a.g[jc] = c * in.gj;
+    st->it = in.it + 1;
+    const double rec = fabs(gnew) / in.nb;
     a.hist[jc] = rec;
     st->last_rec = rec;
-    const bool finite = isfinite(st->omega) && isfinite(t) && isfinite(gnew);
-    const bool conv = fabs(gnew) <= st->tau_nb;
+    const bool finite = isfinite(omega) && isfinite(t) && isfinite(gnew);
+    const bool conv = fabs(gnew) <= in.tau_nb;
     if (brk)
-        st->breakdowns += 1;
+        st->breakdowns = in.breakdowns + 1;
     a.flags[jc] = (reorth ? 1 : 0) | (brk ? 2 : 0) | (hard ? 4 : 0);
     st->jeff = j;
     if (!finite)
         st->nonfinite = 1;
-    if (brk || conv || st->it >= st->maxiter || !finite || j == m) {
+    if (brk || conv || in.it + 1 >= in.maxiter || !finite || j == in.m) {
         st->done = 1;
         st->conv = conv ? 1 : 0;
     } else {
-        a.scales[j] = make_param(st->fmt, wmax / t).scale;
+        a.scales[j] = make_param(in.fmt, wmax / t).scale;
     }
 }
 
@@ -228,8 +243,8 @@ __device__ void finish_step(DevState *st, const StepArrays &a, int j, bool reort
         carry = rotate_column(lh, j, a.cs, a.sn, a.H + (size_t)(j - 1) * (st->m + 1), pa, pb);
     }
     if (tid == 0)
-        close_step(st, a, j, reorth, st->hard != 0, st->t, reorth ? t2 : st->t,
-                   reorth ? wmax2 : st->wmax, carry);
+        close_step(st, a, load_close(st, a, j), j, reorth, st->hard != 0, st->omega, st->t,
+                   reorth ? t2 : st->t, reorth ? wmax2 : st->wmax, carry);
 }
 
 // ---------------------------------------------------------------------------
@@ -1275,16 +1290,16 @@ __device__ __forceinline__ double shared_load(const double *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Counts the calling blocks of a launch; true in the block that arrives
-// last, when every other block's shared_stores have completed (each waits
-// for its own before it counts).  Block-uniform call; the stores before it
-// come from thread 0.  The last block leaves the counter at 0 for the next
-// launch.
+// Counts the calling blocks of a launch (or of one tile); true in the block
+// that arrives last, when every other block's shared_stores have completed
+// (each thread waits for its own before its block counts).  Block-uniform
+// call.  The last block leaves the counter at 0 for the next launch.
 __device__ bool last_block(uint32_t *ticket, uint32_t blocks)
 {
     __shared__ int last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
     if (threadIdx.x == 0) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         const uint32_t at =
             __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         last = at == blocks - 1;
@@ -1329,7 +1344,8 @@ __device__ __forceinline__ double wave_fold(const double *__restrict__ src, int 
 // The whole block folds src[0 .. nb): wave w takes the contiguous quarter
 // starting at w * ceil(nb / 4), and the four wave totals are combined in
 // wave order (so the result depends on nb only, not on timing).  Every
-// thread returns the total; block-uniform call.
+// thread returns the total; block-uniform call.  (thread_fold below has the
+// same order for few partials.)
 template <bool SHARED = false>
 __device__ double block_fold(const double *__restrict__ src, int nb, bool is_max)
 {
@@ -1346,6 +1362,57 @@ __device__ double block_fold(const double *__restrict__ src, int nb, bool is_max
     for (int w = 1; w < RWAVES; ++w)
         t = is_max ? fmax(t, part[w]) : t + part[w];
     __syncthreads();
+    return t;
+}
+
+// A sum and a max of the same length, their loads in flight together; each as
+// block_fold.
+template <bool SHARED>
+__device__ void block_fold2(const double *__restrict__ s0, const double *__restrict__ s1, int nb,
+                            double &sum, double &mx)
+{
+    __shared__ double part[2][RWAVES];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int q = (nb + RWAVES - 1) / RWAVES;
+    const int lo = min(wave * q, nb), hi = min(lo + q, nb);
+    const double a = wave_fold<SHARED>(s0 + lo, hi - lo, false);
+    const double b = wave_fold<SHARED>(s1 + lo, hi - lo, true);
+    if (lane == 0) {
+        part[0][wave] = a;
+        part[1][wave] = b;
+    }
+    __syncthreads();
+    sum = part[0][0];
+    mx = part[1][0];
+#pragma unroll
+    for (int w = 1; w < RWAVES; ++w) {
+        sum = sum + part[0][w];
+        mx = fmax(mx, part[1][w]);
+    }
+    __syncthreads();
+}
+
+// block_fold of nb <= SMALL_TILES sums by one thread, in the same order: each
+// quarter as the wave butterfly leaves it on lane 0, then the quarters.
+constexpr int SMALL_TILES = 8;
+__device__ __forceinline__ double thread_fold(const double *__restrict__ src, int nb)
+{
+    constexpr int Q = SMALL_TILES / RWAVES;              // partials of a quarter, at most
+    static_assert(Q == 2, "a quarter of two partials: their sum");
+    double x[RWAVES][Q];
+    const int q = (nb + RWAVES - 1) / RWAVES;
+#pragma unroll
+    for (int w = 0; w < RWAVES; ++w)
+#pragma unroll
+        for (int i = 0; i < Q; ++i)
+            x[w][i] = src[min(w * q + i, nb - 1)];
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < RWAVES; ++w) {
+        const int left = min(q, nb - w * q);
+        const double a = (left > 0 ? x[w][0] : 0.0) + (left > 1 ? x[w][1] : 0.0);
+        t = w == 0 ? a : t + a;
+    }
     return t;
 }
 
@@ -1374,21 +1441,35 @@ constexpr int HARD_BLOCKS = 256;
 // not stored), so a wave keeps NK * UL loads of G in flight instead of
 // walking its columns one after another; LOADS (a multiple of 8) is about
 // how many.
-template <int NK, int LOADS>
+// NEWEST: row and column `last` come from lg instead of G (from the column
+// block of the same launch, which writes them there); k0 is the column that
+// out[0] belongs to.
+template <int NK, int LOADS, bool NEWEST>
 __device__ __forceinline__ void gram_times_h(const double *__restrict__ G, size_t ldg,
-                                             const double *lh, int j, int l0, int l1, int lane,
-                                             double *out)
+                                             const double *lh, const double *lg, int last, int k0,
+                                             int j, int l0, int l1, int lane, double *out)
 {
     constexpr int UL = LOADS / 8 * (NK == 1 ? 8 : NK == 2 ? 4 : NK == 3 ? 3 : 2);
     int kc[NK];
     double acc[NK];
 #pragma unroll
     for (int q = 0; q < NK; ++q) {
-        kc[q] = min(lane + 64 * q, j - 1);
+        kc[q] = min(lane + 64 * q, NEWEST ? max(last - k0 - 1, 0) : j - 1);
         acc[q] = 0.0;
     }
+    auto entry = [&](double g, int l, int q) {
+        if constexpr (NEWEST) {
+            const int k = k0 + lane + 64 * q;
+            if (l == last)
+                g = lg[min(k, last)];
+            if (k == last)
+                g = lg[l];
+        }
+        return g;
+    };
     int l = l0;
-    for (; l + UL <= l1; l += UL) {
+    const int le = NEWEST ? min(l1, last) : l1;          // rows in G
+    for (; l + UL <= le; l += UL) {
         double g[UL][NK];
 #pragma unroll
         for (int u = 0; u < UL; ++u)
@@ -1400,14 +1481,16 @@ __device__ __forceinline__ void gram_times_h(const double *__restrict__ G, size_
             const double hl = lh[l + u];
 #pragma unroll
             for (int q = 0; q < NK; ++q)
-                acc[q] = fma(g[u][q], hl, acc[q]);
+                acc[q] = fma(entry(g[u][q], l + u, q), hl, acc[q]);
         }
     }
     for (; l < l1; ++l) {
         const double hl = lh[l];
 #pragma unroll
-        for (int q = 0; q < NK; ++q)
-            acc[q] = fma(G[(size_t)l * ldg + kc[q]], hl, acc[q]);
+        for (int q = 0; q < NK; ++q) {
+            const double g = l < le ? G[(size_t)l * ldg + kc[q]] : 0.0;
+            acc[q] = fma(entry(g, l, q), hl, acc[q]);
+        }
     }
 #pragma unroll
     for (int q = 0; q < NK; ++q)
@@ -1426,7 +1509,15 @@ __device__ __forceinline__ void gram_times_h(const double *__restrict__ G, size_
 // before, 15 us deep, 19 us shallow); shallow rings hold 4 (8 in fp64), which
 // keeps the blocks of a full grid closer together in the basis: at 128^3
 // fp16, 512 tiles, j to 100, 43.7 us shallow, 49.3 us deep, 43.2 us before.
-template <int F, int ROLE, bool DEEP>
+//
+// RU_SMALL (U_CGS2 with `close` on at most SMALL_TILES tiles, where a step is
+// launches and their latency): the prologue also folds the multi-dot's and
+// the SpMV's partials, which saves that launch (5 us); each of a tile's CH
+// chunks has a block of its own; and the block that finishes last forms all
+// norms from w, tile by tile in the order of the other forms (same bits).
+enum { RU_SHALLOW = 0, RU_DEEP = 1, RU_SMALL = 2 };
+
+template <int F, int ROLE, int MODE>
 __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, int64_t ld,
                                                 const double *__restrict__ scales, int n, int j_arg,
                                                 const double *__restrict__ coef,
@@ -1435,7 +1526,8 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
                                                 const DevState *st,
                                                 double *__restrict__ uio, DevState *stw,
                                                 const double *__restrict__ G, StepArrays sa,
-                                                int nb_first, int close)
+                                                int nb_first, int close,
+                                                const double *__restrict__ spmv_part, int nb_spmv)
 {
     int j = j_arg;
     if constexpr (ROLE == U_STEP1 || ROLE == U_STEP2 || ROLE == U_STEP1N || ROLE == U_CGS2 ||
@@ -1455,26 +1547,41 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
     }
     using T = Fmt<F>;
     using Tile = VecTile<F>;
-    constexpr int VW = T::VW, CH = T::CH, UNR = DEEP ? 4 / CH : CH == 1 ? 2 : 1;
-    constexpr int RING = DEEP ? 4 : 2;
+    constexpr bool SMALL = MODE == RU_SMALL;
+    static_assert(!SMALL || ROLE == U_CGS2, "small steps are one-pass updates");
+    constexpr int VW = T::VW, CH = T::CH;
+    constexpr int CHL = SMALL ? 1 : CH;               // chunks of the tile this block streams
+    constexpr int UNR = MODE != RU_SHALLOW ? 4 / CHL : CH == 1 ? 2 : 1;
+    constexpr int RING = MODE != RU_SHALLOW ? 4 : 2;
     const int64_t ldb = ld * fmt_bytes(F);
     const int64_t ntiles = ((int64_t)n + Tile::ROWS - 1) / Tile::ROWS;
     double ssq = 0.0, mx = 0.0;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     Tile vt;
-    u32x4 ring[RING][UNR][CH];
+    u32x4 ring[RING][UNR][CHL];
+    // w ahead of its use, where the registers are there for it
+    constexpr bool PREW = MODE != RU_SHALLOW && ROLE != U_COMBINE;
+    double wpre[PREW ? CHL * VW : 1];
     auto load_batch = [&](int r, int k0) {
 #pragma unroll
         for (int u = 0; u < UNR; ++u)
 #pragma unroll
-            for (int c = 0; c < CH; ++c)
+            for (int c = 0; c < CHL; ++c)
                 ring[r][u][c] = vt.load(k0 + u, j, c);
     };
+    const int c0 = SMALL ? (int)blockIdx.x % CH : 0;  // first chunk streamed
+    const int64_t tile0 = SMALL ? blockIdx.x / CH : blockIdx.x;
     auto start_tile = [&](int64_t tile) {
         vt.set(V, ldb, tile, n);
+        if constexpr (SMALL)
+            vt.voff[0] = vt.row(c0) < n ? (uint32_t)(c0 * BLK + tid) * 16u : 0u;
 #pragma unroll
         for (int r = 0; r < RING; ++r)
             load_batch(r, r * UNR);
+        if constexpr (PREW)
+#pragma unroll
+            for (int c = 0; c < CHL; ++c)
+                load_w<VW>(w, n, vt.row(c0 + c), wpre + c * VW);
     };
     // U_CGS2: Gram-form re-dot u = h - G h, then steps 5-10 in one update;
     // U_HARD: the explicit second pass of a hard step.  lp holds partial sums
@@ -1488,7 +1595,7 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
     // coefficients and scales, the coefficients 0 up to a whole batch beyond j
     // (the kernel-level calls take one vector more than a solve's restart)
     __shared__ double lc[MAX_RESTART + 1 + UNR], lsc[T::SCALED ? MAX_RESTART + 1 + UNR : 1];
-    __shared__ double lh[ONEPASS ? MAX_RESTART : 1];
+    __shared__ double lh[ONEPASS ? MAX_RESTART : 1], lg[SMALL ? MAX_RESTART : 1];
     __shared__ double lp[ONEPASS ? NWAVE * MAX_RESTART : 1];
     __shared__ double lr[2][NWAVE];
     const int ntb = ONEPASS ? (int)gridDim.x - 1 : (int)gridDim.x;    // blocks with tiles
@@ -1501,8 +1608,8 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
         if (tid == 0)
             shared_store(&stw->carry, carry);
     };
-    if ((int)blockIdx.x < ntb && blockIdx.x < ntiles)
-        start_tile(blockIdx.x);
+    if ((int)blockIdx.x < ntb && tile0 < ntiles)
+        start_tile(tile0);
     if constexpr (T::SCALED)
         for (int k = tid; k < j + UNR; k += BLK)
             lsc[k] = k < j ? scales[k] : 1.0;
@@ -1513,22 +1620,97 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
     // launch and the second pass's (5.4 and 4.5 us of a step) on every step
     // that is not hard; a hard step pauses the cycle for the host, which runs
     // the second pass and the close as launches of their own.
-    auto close_cycle_step = [&]() {
-        if (!last_block(&stw->ticket, gridDim.x))
-            return;
-        if (hard) {
-            if (tid == 0) {
-                stw->hard = 1;
-                stw->done = CYCLE_PAUSED;
+    double omega = 0.0;
+    CloseIn cin{};
+    if constexpr (ROLE == U_CGS2)
+        if (close)
+            cin = load_close(st, sa, j);
+    // Fig. 1 step 8 for a tile's rows x (0 beyond n): u_k += dec(V_k)^T x, one
+    // wave sum per vector added into the wave's slot of lp
+    auto redot = [&](const Tile &tl, const double *x) {
+        for (int k = 0; k < j; ++k) {
+            const double sk = T::SCALED ? scales[k] : 1.0;
+            const uint8_t *Vk = V + (int64_t)k * ldb;
+            double acc = 0.0;
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                double d[VW];
+                load_dec<F>(Vk, tl.row(c), n, sk, d);
+#pragma unroll
+                for (int e = 0; e < VW; ++e)
+                    acc = fma(d[e], x[c * VW + e], acc);
             }
-            return;
+            acc = wave_sum(acc);
+            if (lane == 0)
+                lp[k * NWAVE + wv] += acc;
         }
-        const double a0 = block_fold<true>(ra.part, ntb, false);
-        const double a1 = block_fold<true>(ra.part + ra.stride, ntb, true);
+    };
+    auto redot_out = [&](int64_t slot) {
+        __syncthreads();
+        for (int k = tid; k < j; k += BLK) {
+            double a = lp[k * NWAVE];
+#pragma unroll
+            for (int w2 = 1; w2 < NWAVE; ++w2)
+                a += lp[k * NWAVE + w2];
+            ra.part[(size_t)k * ra.stride + slot] = a;
+        }
+    };
+    auto close_cycle_step = [&]() {
+        const int nparts = (int)ntiles < ntb ? (int)ntiles : ntb;
+        if (!last_block(&stw->ticket, SMALL ? gridDim.x : (unsigned)nparts + 1u))
+            return;
+        double a0 = 0.0, a1 = 0.0;
+        if constexpr (SMALL) {
+            // every block has stored its chunk of w
+            double *nrm = lg;                   // the newest Gram row is done with
+            for (int64_t t = 0; t < ntiles; ++t) {
+                Tile tl;
+                tl.set(V, ldb, t, n);
+                double x[CH * VW];
+#pragma unroll
+                for (int c = 0; c < CH; ++c)
+#pragma unroll
+                    for (int e = 0; e < VW; ++e)
+                        x[c * VW + e] =
+                            tl.row(c) + e < n ? shared_load(w + tl.row(c) + e) : 0.0;
+                double sq = 0.0, mt = 0.0;
+#pragma unroll
+                for (int e = 0; e < CH * VW; ++e) {
+                    sq = fma(x[e], x[e], sq);
+                    mt = fmax(mt, fabs(x[e]));
+                }
+                if (hard) {
+                    for (int k = tid; k < NWAVE * j; k += BLK)
+                        lp[k] = 0.0;
+                    __syncthreads();
+                    redot(tl, x);
+                    redot_out(t);
+                }
+                block_sum_max(sq, mt);
+                if (tid == 0) {
+                    if (hard) {
+                        ra.part[(size_t)j * ra.stride + t] = sq;
+                        ra.part[(size_t)(j + 1) * ra.stride + t] = mt;
+                    }
+                    nrm[t] = sq;
+                    a1 = fmax(a1, mt);
+                }
+            }
+            if (tid == 0)
+                a0 = thread_fold(nrm, (int)ntiles);
+        } else if (!hard) {
+            block_fold2<true>(ra.part, ra.part + ra.stride, nparts, a0, a1);
+        }
         if (tid == 0) {
-            stw->hard = 0;
-            stw->reorth = ro ? 1 : 0;
-            close_step(stw, sa, j, ro, false, t1, sqrt(a0), a1, shared_load(&stw->carry));
+            stw->omega = omega;
+            stw->hard = hard ? 1 : 0;
+            if (hard) {
+                stw->done = CYCLE_PAUSED;
+            } else {
+                stw->reorth = ro ? 1 : 0;
+                close_step(stw, sa, cin, j, ro, false, omega, t1, sqrt(a0), a1,
+                           shared_load(&stw->carry));
+            }
         }
     };
     if constexpr (ROLE == U_CGS2) {
@@ -1539,22 +1721,60 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
         // with h + u (re-orthogonalising) or h.  Without `close`, block 0
         // publishes the decision and t1 for the closing fold.  A hard step
         // updates with h only and adds the explicit re-dot of the result.
-        for (int k = tid; k < j; k += BLK)
-            lh[k] = coef[k];
-        __syncthreads();
         const size_t ldg = (size_t)st->m + 1;
+        if constexpr (SMALL) {
+            // the SpMV's partials are at most one per lane here: in flight
+            // with the multi-dot's
+            const int q4 = (nb_spmv + RWAVES - 1) / RWAVES;
+            const int lo = min(wv * q4, nb_spmv), cnt = min(q4, nb_spmv - lo);
+            const double om = lane < cnt ? spmv_part[lo + lane] : 0.0;
+            for (int e = tid; e < 2 * j; e += BLK) {
+                const int k = e < j ? e : e - j;
+                const double a =
+                    thread_fold(ra.part + (size_t)(e < j ? k : j + 2 + k) * ra.stride, nb_first);
+                if (e < j) {
+                    lh[k] = a;
+                    if (blockIdx.x == 0)
+                        sa.h[k] = a;                    // for a hard step's second pass
+                } else {
+                    lg[k] = a;
+                    if (colblk) {
+                        sa.G[(size_t)(j - 1) * ldg + k] = a;
+                        sa.G[(size_t)k * ldg + (j - 1)] = a;
+                    }
+                }
+            }
+            const double oq = wave_sum(0.0 + om);
+            if (lane == 0)
+                lr[0][wv] = oq;
+            __syncthreads();
+            double o2 = lr[0][0];
+#pragma unroll
+            for (int w2 = 1; w2 < RWAVES; ++w2)
+                o2 += lr[0][w2];
+            omega = sqrt(o2);
+        } else {
+            for (int k = tid; k < j; k += BLK)
+                lh[k] = coef[k];
+            omega = st->omega;
+        }
+        __syncthreads();
         const int q = (j + NWAVE - 1) / NWAVE;
         const int l0 = min(wv * q, j), l1 = min(l0 + q, j);
         constexpr int GL = 16;
         double *lpw = lp + wv * MAX_RESTART;
+        auto gram = [&](auto nk, int k0) __attribute__((always_inline)) {
+            gram_times_h<decltype(nk)::value, GL, SMALL>(G + k0, ldg, lh, lg, j - 1, k0, j - k0, l0,
+                                                         l1, lane, lpw + k0);
+        };
         switch ((j + 63) / 64) {
-        case 1: gram_times_h<1, GL>(G, ldg, lh, j, l0, l1, lane, lpw); break;
-        case 2: gram_times_h<2, GL>(G, ldg, lh, j, l0, l1, lane, lpw); break;
-        case 3: gram_times_h<3, GL>(G, ldg, lh, j, l0, l1, lane, lpw); break;
-        case 4: gram_times_h<4, GL>(G, ldg, lh, j, l0, l1, lane, lpw); break;
+        case 1: gram(std::integral_constant<int, 1>{}, 0); break;
+        case 2: gram(std::integral_constant<int, 2>{}, 0); break;
+        case 3: gram(std::integral_constant<int, 3>{}, 0); break;
+        case 4: gram(std::integral_constant<int, 4>{}, 0); break;
         default:
             for (int k0 = 0; k0 < j; k0 += 256)
-                gram_times_h<4, GL>(G + k0, ldg, lh, j - k0, l0, l1, lane, lpw + k0);
+                gram(std::integral_constant<int, 4>{}, k0);
             break;
         }
         __syncthreads();
@@ -1582,7 +1802,6 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
             hh += lr[0][w2];
             hu += lr[1][w2];
         }
-        const double omega = st->omega;
         const double t1sq = omega * omega - hh - hu;
         hard = !(t1sq >= HARD_RATIO * omega * omega);       // also when not finite
         t1 = hard ? 0.0 : sqrt(t1sq);
@@ -1658,14 +1877,14 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
     if (tid < UNR)
         lc[j + tid] = 0.0;
     __syncthreads();
-    for (int64_t tile = blockIdx.x; tile < ntiles; tile += ntb) {
-        if (tile != blockIdx.x)
+    for (int64_t tile = tile0; tile < ntiles; tile += ntb) {
+        if (tile != tile0)
             start_tile(tile);
         double s[CH * VW];
         int64_t i0[CH];
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            i0[c] = vt.row(c);
+        for (int c = 0; c < CHL; ++c) {
+            i0[c] = vt.row(c0 + c);
 #pragma unroll
             for (int e = 0; e < VW; ++e)
                 s[c * VW + e] = 0.0;
@@ -1676,7 +1895,7 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
                 const double ck = lc[k0 + u];
                 const double sk = T::SCALED ? lsc[k0 + u] : 1.0;
 #pragma unroll
-                for (int c = 0; c < CH; ++c) {
+                for (int c = 0; c < CHL; ++c) {
                     double d[VW];
                     T::dec(ring[r][u][c], sk, d);
 #pragma unroll
@@ -1703,21 +1922,33 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
         if (!vt.full) {
             // rows >= n took whatever their chunk holds
 #pragma unroll
-            for (int c = 0; c < CH; ++c)
+            for (int c = 0; c < CHL; ++c)
 #pragma unroll
                 for (int e = 0; e < VW; ++e)
                     if (i0[c] + e >= n)
                         s[c * VW + e] = 0.0;
         }
+        if constexpr (SMALL) {
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
+            for (int e = 0; e < VW; ++e)
+                if (i0[0] + e < n)
+                    shared_store(w + i0[0] + e, wpre[e] - s[e]);
+        }
+#pragma unroll
+        for (int c = 0; c < (SMALL ? 0 : CH); ++c) {
             double o[VW];
             if constexpr (ROLE == U_COMBINE) {
 #pragma unroll
                 for (int e = 0; e < VW; ++e)
                     o[e] = s[c * VW + e];
             } else if constexpr (ROLE == U_SOLUTION) {
-                load_w<VW>(w, n, i0[c], o);
+                if constexpr (PREW) {
+#pragma unroll
+                    for (int e = 0; e < VW; ++e)
+                        o[e] = wpre[c * VW + e];
+                } else {
+                    load_w<VW>(w, n, i0[c], o);
+                }
                 if (dinv) {
                     double dv[VW];
                     load_w<VW>(dinv, n, i0[c], dv);
@@ -1730,40 +1961,26 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
                         o[e] = o[e] + s[c * VW + e];
                 }
             } else {
-                load_w<VW>(w, n, i0[c], o);
+                if constexpr (PREW) {
+#pragma unroll
+                    for (int e = 0; e < VW; ++e)
+                        o[e] = wpre[c * VW + e];
+                } else {
+                    load_w<VW>(w, n, i0[c], o);
+                }
 #pragma unroll
                 for (int e = 0; e < VW; ++e) {
                     o[e] = o[e] - s[c * VW + e];
-                    ssq += o[e] * o[e];
+                    ssq = fma(o[e], o[e], ssq);
                     mx = fmax(mx, fabs(o[e]));
                     s[c * VW + e] = o[e];        // kept for a hard step's re-dot
                 }
             }
             store_w<VW>(w, n, i0[c], o);
         }
-        if constexpr (ROLE == U_CGS2) {
-            if (hard) {
-                // Fig. 1 step 8 for this tile's rows: u_k += dec(V_k)^T w1
-                // (rows >= n hold w1 = 0); one wave sum per vector, added
-                // into the wave's slot in tile order
-                for (int k = 0; k < j; ++k) {
-                    const double sk = T::SCALED ? scales[k] : 1.0;
-                    const uint8_t *Vk = V + (int64_t)k * ldb;
-                    double acc = 0.0;
-#pragma unroll
-                    for (int c = 0; c < CH; ++c) {
-                        double d[VW];
-                        load_dec<F>(Vk, i0[c], n, sk, d);
-#pragma unroll
-                        for (int e = 0; e < VW; ++e)
-                            acc = fma(d[e], s[c * VW + e], acc);
-                    }
-                    acc = wave_sum(acc);
-                    if (lane == 0)
-                        lp[k * NWAVE + wv] += acc;
-                }
-            }
-        }
+        if constexpr (ROLE == U_CGS2 && !SMALL)
+            if (hard)
+                redot(vt, s);
     }
     if constexpr (ROLE == U_SOLUTION || ROLE == U_COMBINE || ROLE == U_STEP1)
         return;
@@ -1771,16 +1988,13 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
     // the re-dot in rows 0..j-1 and the norms in rows j, j+1, its second
     // pass the norms in rows j+2, j+3
     int row = 0;
+    if constexpr (SMALL) {
+        close_cycle_step();
+        return;
+    }
     if constexpr (ROLE == U_CGS2) {
         if (hard) {
-            __syncthreads();
-            for (int k = tid; k < j; k += BLK) {
-                double a = lp[k * NWAVE];
-#pragma unroll
-                for (int w2 = 1; w2 < NWAVE; ++w2)
-                    a += lp[k * NWAVE + w2];
-                ra.part[(size_t)k * ra.stride + blockIdx.x] = a;
-            }
+            redot_out(tile0);
             row = j;
         }
     }
@@ -1788,8 +2002,8 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
         row = j + 2;
     block_sum_max(ssq, mx);
     if (threadIdx.x == 0) {
-        shared_store(ra.part + (size_t)row * ra.stride + blockIdx.x, ssq);
-        shared_store(ra.part + (size_t)(row + 1) * ra.stride + blockIdx.x, mx);
+        shared_store(ra.part + (size_t)row * ra.stride + tile0, ssq);
+        shared_store(ra.part + (size_t)(row + 1) * ra.stride + tile0, mx);
     }
     if constexpr (ROLE == U_CGS2)
         if (close)
@@ -2749,25 +2963,52 @@ __global__ __launch_bounds__(BLK) void k_decode(const uint8_t *__restrict__ Q, i
 
 // Back substitution R y = g for the cycle's least-squares problem (Fig. 1
 // step 17); R is the rotated Hessenberg matrix.  One wavefront, column
-// oriented: y_i = g_i / R_ii, then g_k -= R_ki y_i for k < i in parallel.
+// oriented: y_i = g_i / R_ii, then g_k -= R_ki y_i for k < i in parallel.  A
+// chain of jeff divisions: lane l keeps rows l, l + 64, ... in registers and
+// the next PF columns are in flight, so a column costs its division and a
+// lane read (61 us for 100 columns with each column loaded in its turn and
+// g in LDS, 15 us now).  Rows >= i take garbage from column i, but they are
+// done.
+template <int NQ>
 __global__ __launch_bounds__(64) void k_backsolve(const DevState *st, StepArrays sa)
 {
-    __shared__ double gl[MAX_RESTART + 2];
-    __shared__ double yi;
-    const int jeff = st->jeff, m = st->m;
-    for (int i = threadIdx.x; i < jeff; i += 64)
-        gl[i] = sa.g[i];
-    __syncthreads();
-    for (int i = jeff - 1; i >= 0; --i) {
-        if (threadIdx.x == 0) {
-            yi = gl[i] / sa.H[(size_t)i * (m + 1) + i];
-            sa.y[i] = yi;
+    constexpr int PF = 8;
+    const int jeff = st->jeff, m = st->m, lane = threadIdx.x;
+    if (jeff == 0)
+        return;
+    double g[NQ], col[PF][NQ];
+    auto load = [&](int p, int i) {
+        const double *Hi = sa.H + (size_t)min(max(i, 0), jeff - 1) * (m + 1);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+            col[p][q] = Hi[min(lane + 64 * q, m)];
+    };
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+        g[q] = sa.g[min(lane + 64 * q, m)];
+#pragma unroll
+    for (int p = 0; p < PF; ++p)
+        load(p, 64 * NQ - 1 - p);
+#pragma unroll
+    for (int q = NQ - 1; q >= 0; --q) {
+        for (int l0 = 63; l0 >= 0; l0 -= PF) {
+#pragma unroll
+            for (int p = 0; p < PF; ++p) {
+                const int l = l0 - p, i = 64 * q + l;
+                if (i < jeff) {
+                    const double yl = g[q] / col[p][q];
+                    const double y = __hiloint2double(
+                        __builtin_amdgcn_readlane(__double2hiint(yl), l),
+                        __builtin_amdgcn_readlane(__double2loint(yl), l));
+#pragma unroll
+                    for (int r = 0; r <= q; ++r)
+                        g[r] = fma(-col[p][r], y, g[r]);
+                    if (lane == 0)
+                        sa.y[i] = y;
+                }
+                load(p, i - PF);
+            }
         }
-        __syncthreads();
-        const double* Hi = sa.H + (size_t)i * (m + 1);
-        for (int k = threadIdx.x; k < i; k += 64)
-            gl[k] -= Hi[k] * yi;
-        __syncthreads();
     }
 }
 
@@ -3105,6 +3346,8 @@ void launch_multidot(const OrthArgs &a, hipStream_t s)
 #undef CBG_MD
 }
 
+bool small_step(int fmt, int64_t n) { return orth_grid(fmt, n) <= SMALL_TILES; }
+
 void launch_update(const OrthArgs &a, hipStream_t s)
 {
     // the one-pass roles run one block more: the column block
@@ -3121,21 +3364,27 @@ void launch_update(const OrthArgs &a, hipStream_t s)
         CBG_FMT_SWITCH(a.fmt, (hipExtLaunchKernelGGL(k_update<F, R, D>, dim3(g), dim3(BLK), 0, \
                                                      s, a.ev0, a.ev1, 0, V, a.ld, a.scales,   \
                                                      a.n, a.j, a.coef, a.wio, a.dinv, ra,     \
-                                                     a.st, a.u, a.stw, a.G, sa, g0,           \
-                                                     a.close)))                               \
+                                                     a.st, a.u, a.stw, a.G, sa, g0, a.close,  \
+                                                     a.ws.spmv, a.nb_spmv)))                  \
     } else {                                                                                  \
-        CBG_FMT_SWITCH(a.fmt, (k_update<F, R, D><<<g, BLK, 0, s>>>(V, a.ld, a.scales, a.n,    \
-                                                                    a.j, a.coef, a.wio,       \
-                                                                    a.dinv, ra, a.st, a.u,    \
-                                                                    a.stw, a.G, sa, g0,       \
-                                                                    a.close)))                \
+        CBG_FMT_SWITCH(a.fmt, (k_update<F, R, D><<<g, BLK, 0, s>>>(                           \
+                                  V, a.ld, a.scales, a.n, a.j, a.coef, a.wio, a.dinv, ra,     \
+                                  a.st, a.u, a.stw, a.G, sa, g0, a.close, a.ws.spmv,          \
+                                  a.nb_spmv)))                                                \
     }
     // deep rings below two tiles per CU (see k_update)
 #define CBG_UPD(R)                                                                            \
     if (g0 < FULL_GRID) {                                                                     \
-        CBG_UPDL(R, true)                                                                     \
+        CBG_UPDL(R, RU_DEEP)                                                                  \
     } else {                                                                                  \
-        CBG_UPDL(R, false)                                                                    \
+        CBG_UPDL(R, RU_SHALLOW)                                                               \
+    }
+    if (a.nb_spmv > 0) {                                        // a small step (small_step)
+        int ch = 1;
+        CBG_FMT_SWITCH(a.fmt, (ch = Fmt<F>::CH))
+        const int g = g0 * ch + 1;
+        CBG_UPDL(U_CGS2, RU_SMALL)
+        return;
     }
     switch (a.role) {
     case U_PLAIN: CBG_UPD(U_PLAIN) break;
@@ -3366,9 +3615,17 @@ void launch_fill_zero(double *p, int count, hipStream_t s)
         k_fill_zero<<<grid_for(count, 256), 256, 0, s>>>(p, count);
 }
 
-void launch_backsolve(const DevState *st, const void *sa, hipStream_t s)
+void launch_backsolve(const DevState *st, const void *sa, int m, hipStream_t s)
 {
-    k_backsolve<<<1, 64, 0, s>>>(st, *(const StepArrays *)sa);
+    const StepArrays &a = *(const StepArrays *)sa;
+    if (m <= 64)
+        k_backsolve<1><<<1, 64, 0, s>>>(st, a);
+    else if (m <= 128)
+        k_backsolve<2><<<1, 64, 0, s>>>(st, a);
+    else if (m <= 256)
+        k_backsolve<4><<<1, 64, 0, s>>>(st, a);
+    else
+        k_backsolve<8><<<1, 64, 0, s>>>(st, a);
 }
 
 size_t step_arrays_size() { return sizeof(StepArrays); }

@@ -59,6 +59,8 @@ struct OrthArgs {
     const double *G;      // one-pass update: the Gram matrix of the stored basis
     const void *sa;       // one-pass update: the step arrays (H, cs, sn) of the column block
     int close;            // one-pass update: its last block closes the step
+    int nb_spmv;          // one-pass update with close on a small_step: the SpMV's partials,
+                          // folded with the multi-dot's by the update itself (else 0)
     const double *coef;   // update coefficients
     double *wio;          // update: the vector updated in place (or written)
     const double *dinv;
@@ -93,6 +95,9 @@ void launch_sell_fill(int n, const int32_t *rp, const int32_t *ci, const double 
                       int64_t nslice, const int64_t *sp, int32_t *sc, double *sv, hipStream_t s);
 void launch_multidot(const OrthArgs &a, hipStream_t s);
 void launch_update(const OrthArgs &a, hipStream_t s);
+// Whether a step's vectors are few enough tiles for the update to fold the
+// multi-dot's partials itself (RU_SMALL).
+bool small_step(int fmt, int64_t n);
 // Fused update + re-dot with norms (w -= V coef; partials of V^T w, ||w||^2,
 // max|w| as the multi-dot with norms).  Returns the grid size (the number of
 // partials per value), or 0 if j is beyond the fused kernel's register tile
@@ -152,7 +157,7 @@ void launch_jacobi_setup(const SpmvArgs &a, int64_t ld, double *dinv, unsigned *
 void launch_resume(DevState *st, hipStream_t s);
 void launch_clear_flags(DevState *st, unsigned *bad, hipStream_t s);
 void launch_fill_zero(double *p, int count, hipStream_t s);
-void launch_backsolve(const DevState *st, const void *sa, hipStream_t s);
+void launch_backsolve(const DevState *st, const void *sa, int m, hipStream_t s);
 size_t step_arrays_size();
 void make_step_arrays(void *out, double *H, double *h, double *u, double *cs, double *sn,
                       double *g, double *y, double *hist, double *scales, int32_t *flags);

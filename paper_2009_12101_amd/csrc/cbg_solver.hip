@@ -239,6 +239,9 @@ struct CycleEvents {
 // launches that find the cycle finished and return at once.
 constexpr int STEP_CHUNK = 16;
 
+// Rows up to which steps 13-14 always run inside the next SpMV's gather.
+constexpr int GATHER_MAX_N = 65536;
+
 struct DoneWatch {
     hipEvent_t ev[2] = {nullptr, nullptr};
     int32_t *flag = nullptr;        // pinned: one slot per chunk of a cycle
@@ -442,11 +445,15 @@ int cbgmres_solve(const cbg_csr *A, const double *b, double *x, const cbg_opts *
     // steps 13-14 in a pass of their own, or inside the next SpMV's gather:
     // one division per row against one per nonzero, so long rows favour the
     // pass; with Jacobi the pass also forms dinv .* v once, where the gather
-    // reads dinv per nonzero
+    // reads dinv per nonzero.  (The byte model follows this choice.)
     const bool norm_pass = !vhat && pc0 != CBG_PC_BLOCK_JACOBI &&
         ((opt->flags & CBG_FLAG_NORMALISE_PASS) != 0 ||
          ((opt->flags & CBG_FLAG_NORMALISE_GATHER) == 0 &&
           ((double)A->nnz > 12.0 * n || pc0 == CBG_PC_JACOBI)));
+    // up to GATHER_MAX_N rows the pass would be a launch's latency (4 us), and
+    // the divisions hide behind the gather's loads: the gather forms the same
+    // bits there unless the pass was asked for
+    const bool pass = norm_pass && (n > GATHER_MAX_N || (opt->flags & CBG_FLAG_NORMALISE_PASS));
     // steps whose update and re-dot share one basis pass
     auto fused = [&](int j) { return !gram && fuse && fused_takes(fmt, basis_ld(n), j); };
     ByteModel bm{(double)n, (double)A->nnz, (double)fmt_bytes(fmt)};
@@ -746,7 +753,7 @@ int cbgmres_solve(const cbg_csr *A, const double *b, double *x, const cbg_opts *
                 SpmvArgs a{};
                 a.n = n; a.ldy = ld; a.rp = A->row_ptr; a.ci = A->col_idx; a.fval = opt->p_val;
                 a.y = W.z; a.ws = W.red; a.role = 0 /*SR_NONE*/; a.sg = sg; a.st = W.st;
-                if (norm_pass) {
+                if (pass) {
                     launch_step_normalize(fmt, cur, n, ld, nullptr, W.v, slot, W.scales + (j - 1),
                                           W.st, s);
                     a.x = W.v; a.mode = 3 /*SP_FLOATVAL*/;
@@ -767,7 +774,7 @@ int cbgmres_solve(const cbg_csr *A, const double *b, double *x, const cbg_opts *
                 a.dinv = W.dinv; a.y = nxt; a.ws = W.red; a.role = 1 /*SR_STEP*/;
                 a.sg = sg; a.st = W.st;
                 const int base = pc == CBG_PC_JACOBI ? 1 /*SP_JACOBI*/ : 0 /*SP_PLAIN*/;
-                if (norm_pass) {
+                if (pass) {
                     // z = M^-1 v_j formed by the pass: step 3 is the plain SpMV
                     launch_step_normalize(fmt, cur, n, ld, pc == CBG_PC_JACOBI ? W.dinv : nullptr,
                                           W.v, slot, W.scales + (j - 1), W.st, s);
@@ -812,8 +819,10 @@ int cbgmres_solve(const cbg_csr *A, const double *b, double *x, const cbg_opts *
             o.gram = gram ? 1 : 0;
             launch_multidot(o, s);
             o.gram = 0;
-            launch_reduce(W.red, gram ? RR_HG : RR_H, nb_orth, nb_spmv, j, W.st, sa, nullptr,
-                          fmt, s);
+            const bool small = onepass && pause_hard && small_step(fmt, n);
+            if (!small)
+                launch_reduce(W.red, gram ? RR_HG : RR_H, nb_orth, nb_spmv, j, W.st, sa, nullptr,
+                              fmt, s);
             o.coef = W.h; o.role = 1 /*U_STEP1*/;
             timed(1);
             if (onepass) {
@@ -822,6 +831,7 @@ int cbgmres_solve(const cbg_csr *A, const double *b, double *x, const cbg_opts *
                 // met) takes its second pass and the close here
                 o.role = 6 /*U_CGS2*/; o.u = W.u; o.stw = W.st; o.G = W.G; o.sa = sa;
                 o.close = pause_hard ? 1 : 0;
+                o.nb_spmv = small ? nb_spmv : 0;
                 launch_update(o, s);
                 if (!pause_hard)
                     second_pass(j, nxt);
@@ -859,7 +869,7 @@ int cbgmres_solve(const cbg_csr *A, const double *b, double *x, const cbg_opts *
         }
         HIP_TRY(hipGetLastError());
         // step 17: y = R^-1 g ; x += M^-1 V y
-        launch_backsolve(W.st, sa, s);
+        launch_backsolve(W.st, sa, m, s);
         {
             OrthArgs o{};
             o.fmt = fmt; o.V = W.V; o.ld = ld; o.scales = W.scales; o.n = n; o.j = 0;

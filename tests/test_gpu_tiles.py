@@ -46,3 +46,39 @@ def test_tile_edges(orc, dev, fmt, n, j):
     assert np.all(np.abs(w2 - (w - ho @ dec)) <= bound)
     assert abs(norms[0] - np.linalg.norm(w2)) <= 1e-13 * norms[0]
     assert norms[1] == np.abs(w2).max()
+
+
+@pytest.mark.parametrize("fmt", ["fp64", "fp32", "fp16", "e4m3"])
+@pytest.mark.parametrize("nx", [1, 3, 45, 46, 90, 91, 128, 129, 181, 182])
+def test_small_step_edges(orc, dev, fmt, nx):
+    """Steps whose folds run inside the update (up to eight tiles) and the
+    first sizes beyond: one ragged tile, tile counts of 1, 2, 4, 8 and 9 for
+    2048 and 4096 rows.  Three steps with Jacobi, before stored entries can
+    round differently, against the oracle's Fig. 1: residuals and x to 1e-12."""
+    import paper_2009_12101_amd as cbg
+    from paper_2009_12101_amd import problems as P
+    A = P.poisson2d(nx)
+    print(f"small step {fmt} n={A.n}", flush=True)
+    b = P.rhs_uniform(A.n, nx)
+    kw = dict(restart=10, fmt=fmt, tol=0.0, maxiter=3 if nx > 1 else 1, precond="jacobi")
+    o = orc.gmres(A, b, **kw)
+    r = cbg.solve(cbg.DeviceCSR.from_host(A, dev), torch.from_numpy(b).to(dev), **kw)
+    assert r.iterations == o["iterations"]
+    assert np.linalg.norm(r.x.cpu().numpy() - o["x"]) <= 1e-12 * np.linalg.norm(o["x"])
+    assert np.allclose(r.hist, o["hist"], rtol=1e-12, atol=1e-15)
+
+
+@pytest.mark.parametrize("m", [1, 8, 63, 64, 65, 127, 129, 200])
+def test_back_substitution_sizes(orc, dev, m):
+    """Whole cycles of m steps around the back substitution's row counts (64
+    per register): x and the residuals of one fp64 cycle against the oracle."""
+    import paper_2009_12101_amd as cbg
+    from paper_2009_12101_amd import problems as P
+    A = P.convdiff7(12)
+    b = P.rhs_uniform(A.n, m)
+    steps = min(m, 60)                   # the system converges soon after
+    kw = dict(restart=m, fmt="fp64", tol=0.0, maxiter=steps)
+    o = orc.gmres(A, b, **kw)
+    r = cbg.solve(cbg.DeviceCSR.from_host(A, dev), torch.from_numpy(b).to(dev), **kw)
+    assert r.iterations == o["iterations"]
+    assert np.linalg.norm(r.x.cpu().numpy() - o["x"]) <= 1e-8 * np.linalg.norm(o["x"])
