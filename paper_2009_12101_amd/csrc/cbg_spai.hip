@@ -337,18 +337,20 @@ struct WeightsLds {
 __device__ void stage_weights(WeightsLds &L, const uint16_t *__restrict__ wq,
                               const float *__restrict__ prm)
 {
-    for (int e = threadIdx.x; e < NF * NH; e += blockDim.x) {
-        const int in = e / NH, out = e % NH;
-        L.w1t[out * NF + in] = wq[QW1 + e];
-    }
-    for (int e = threadIdx.x; e < NH * NH; e += blockDim.x) {
-        const int in = e / NH, out = e % NH;
-        L.w2t[out * NH + in] = wq[QW2 + e];
-    }
-    for (int e = threadIdx.x; e < NH * NO; e += blockDim.x) {
-        const int in = e / NO, out = e % NO;
-        L.w3t[out * NH + in] = wq[QW3 + e];
-    }
+    // four weights (out .. out + 3 of one input) per load
+    auto put = [&](uint16_t *t, const uint16_t *w, int ins, int outs) {
+        for (int e = 4 * (int)threadIdx.x; e < ins * outs; e += 4 * (int)blockDim.x) {
+            const int in = e / outs, out = e % outs;
+            const uint2 v = *(const uint2 *)(w + e);
+            t[(out + 0) * ins + in] = (uint16_t)v.x;
+            t[(out + 1) * ins + in] = (uint16_t)(v.x >> 16);
+            t[(out + 2) * ins + in] = (uint16_t)v.y;
+            t[(out + 3) * ins + in] = (uint16_t)(v.y >> 16);
+        }
+    };
+    put(L.w1t, wq + QW1, NF, NH);
+    put(L.w2t, wq + QW2, NH, NH);
+    put(L.w3t, wq + QW3, NH, NO);
     for (int e = threadIdx.x; e < NH; e += blockDim.x) {
         L.b1[e] = prm[OB1 + e];
         L.b2[e] = prm[OB2 + e];
@@ -635,75 +637,311 @@ __global__ __launch_bounds__(256) void k_grad_o(int n, const int32_t *__restrict
 }
 
 // ---------------------------------------------------------------------------
-// Batched sparse products over K <= 32 vectors stored row-major (n x K):
-// a 32-lane group per row, lane k for vector k.
+// Batched sparse products over K <= 32 vectors stored row-major (n x K).  A
+// quad (4 lanes) takes a row and each of its lanes 8 of the K values, so one
+// gather instruction fetches 16 rows' worth of an entry and a row's indices
+// and values are loaded once, an entry per lane, and passed around the quad
+// by DPP.  Bound by those gathers from L2 (64 bytes an entry of fp16 vectors,
+// 256 of fp64): at 64^3 and K = 32 the products took 245, 295, 304 and (the
+// gradient's dots) 421 us with a lane per value, one entry of two rows per
+// instruction; 67, 127 and, the last two in one kernel, 127 us now.  With
+// the network's output instead of P's values the first product also forms
+// P, and with dO the last one forms dL/dO, which saves P, dL/dP and two more
+// passes over A (117 us).
+//
+// Lane q's values: k = 8 q + e of the fp16 rows (one 16-byte load) and k =
+// 8 (e / 2) + 2 q + e % 2 of the fp64 rows (four 16-byte loads, 64 bytes of a
+// row per instruction); any other K uses k = q + 4 e, value by value.
 // ---------------------------------------------------------------------------
-enum { MM_PV = 0, MM_AY_MINUS_V = 1, MM_ATR = 2 };
+constexpr int QROWS = 64;               // rows per block: one per quad
 
-template <int MODE>
-__global__ __launch_bounds__(256) void k_spmm(int n, int K, const int32_t *__restrict__ rp,
-                                              const int32_t *__restrict__ ci,
-                                              const double *__restrict__ val,
-                                              const float *__restrict__ fval,
-                                              const double *__restrict__ X,
-                                              const uint16_t *__restrict__ Vh,
-                                              double *__restrict__ Y, double scale,
-                                              double *__restrict__ part)
+// Blocks are dealt to the 8 XCDs in turn; this numbering gives each XCD a
+// contiguous run of row blocks, whose neighbour rows its own L2 then holds (a
+// stencil row's gathers reach the planes before and after it).
+__device__ __forceinline__ int xcd_block()
 {
-    const int k = threadIdx.x & 31, grp = threadIdx.x >> 5, ngrp = blockDim.x >> 5;
-    double ssq = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * ngrp + grp; i < n; i += (int64_t)gridDim.x * ngrp) {
-        if (k >= K)
-            continue;
-        double s = 0.0;
-        for (int p = rp[i]; p < rp[i + 1]; ++p) {
-            const int64_t c = ci[p];
-            if constexpr (MODE == MM_PV) {
-                const _Float16 h = __builtin_bit_cast(_Float16, Vh[c * K + k]);
-                s = fma((double)fval[p], (double)(float)h, s);
-            } else {
-                s = fma(val[p], X[c * K + k], s);
-            }
+    const int nb = gridDim.x, x = blockIdx.x & 7;
+    return x * (nb >> 3) + min(x, nb & 7) + (int)(blockIdx.x >> 3);
+}
+
+template <int CTRL>
+__device__ __forceinline__ int quad(int x)
+{
+    return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, true);
+}
+template <int CTRL>
+__device__ __forceinline__ double quad(double x)
+{
+    return __hiloint2double(quad<CTRL>(__double2hiint(x)), quad<CTRL>(__double2loint(x)));
+}
+template <int CTRL>
+__device__ __forceinline__ float quad(float x)
+{
+    return __int_as_float(quad<CTRL>(__float_as_int(x)));
+}
+constexpr int QUAD_XOR1 = 0xB1, QUAD_XOR2 = 0x4E;
+// the value of the quad's lane t (t known after unrolling)
+template <typename T>
+__device__ __forceinline__ T quad_lane(T x, int t)
+{
+    return t == 0 ? quad<0x00>(x) : t == 1 ? quad<0x55>(x) : t == 2 ? quad<0xAA>(x) : quad<0xFF>(x);
+}
+
+__device__ __forceinline__ double f16_value(uint32_t c)
+{
+    return (double)(float)__builtin_bit_cast(_Float16, (uint16_t)c);
+}
+
+// 8 values of row r of the fp16 vectors
+template <bool K32>
+__device__ __forceinline__ void quad_v(const uint16_t *__restrict__ Vh, int64_t r, int K, int q,
+                                       double *d)
+{
+    if constexpr (K32) {
+        const u32x4 v = *(const u32x4 *)(Vh + r * 32 + q * 8);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            d[2 * e] = f16_value(v[e] & 0xFFFFu);
+            d[2 * e + 1] = f16_value(v[e] >> 16);
         }
-        if constexpr (MODE == MM_AY_MINUS_V) {
-            const _Float16 h = __builtin_bit_cast(_Float16, Vh[i * K + k]);
-            s = s - (double)(float)h;
-            ssq += s * s;
-        }
-        if constexpr (MODE == MM_ATR)
-            s *= scale;
-        Y[i * K + k] = s;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            d[e] = q + 4 * e < K ? f16_value(Vh[r * K + q + 4 * e]) : 0.0;
     }
-    if constexpr (MODE == MM_AY_MINUS_V) {
-        double m = 0.0;
-        block_sum_max(ssq, m);
-        if (threadIdx.x == 0)
-            part[blockIdx.x] = ssq;
+}
+// 8 values of row r of the fp64 vectors, and their store
+template <bool K32>
+__device__ __forceinline__ void quad_x(const double *__restrict__ X, int64_t r, int K, int q,
+                                       double *d)
+{
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+        if constexpr (K32) {
+            const f64x2 v = *(const f64x2 *)(X + r * 32 + 4 * e + 2 * q);
+            d[e] = v.x;
+            d[e + 1] = v.y;
+        } else {
+            d[e] = q + 4 * e < K ? X[r * K + q + 4 * e] : 0.0;
+            d[e + 1] = q + 4 * e + 4 < K ? X[r * K + q + 4 * e + 4] : 0.0;
+        }
     }
 }
 
-// dP_e = sum_k G[row(e)][k] * v_k[col(e)] on A's pattern.
-__global__ __launch_bounds__(256) void k_sddmm(int n, int K, const int32_t *__restrict__ rp,
-                                               const int32_t *__restrict__ ci,
-                                               const double *__restrict__ G,
-                                               const uint16_t *__restrict__ Vh,
-                                               double *__restrict__ dP)
+// From lane q's k = 8 (e / 2) + 2 q + e % 2 to its k = 8 q + e (the same move
+// leads back): a 4 x 4 transpose of pairs within the quad.
+__device__ __forceinline__ void quad_transpose(double *d, int q)
 {
-    const int k = threadIdx.x & 31, grp = threadIdx.x >> 5, ngrp = blockDim.x >> 5;
-    for (int64_t i = (int64_t)blockIdx.x * ngrp + grp; i < n; i += (int64_t)gridDim.x * ngrp) {
-        const double g = k < K ? G[i * K + k] : 0.0;
-        for (int p = rp[i]; p < rp[i + 1]; ++p) {
-            const int64_t c = ci[p];
-            double t = 0.0;
-            if (k < K) {
-                const _Float16 h = __builtin_bit_cast(_Float16, Vh[c * K + k]);
-                t = g * (double)(float)h;
-            }
 #pragma unroll
-            for (int d = 16; d >= 1; d >>= 1)
-                t += __shfl_xor(t, d, 32);
-            if (k == 0)
-                dP[p] = t;
+    for (int b = 1; b <= 2; b <<= 1)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (i & b)
+                continue;
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                double &lo = d[2 * i + e], &hi = d[2 * (i | b) + e];
+                const double send = (q & b) ? lo : hi;
+                const double got = b == 1 ? quad<QUAD_XOR1>(send) : quad<QUAD_XOR2>(send);
+                if (q & b)
+                    lo = got;
+                else
+                    hi = got;
+            }
+        }
+}
+
+// Y = P V.  FROM_O: P_ic = fl32((delta + O[slot]) / a_ii) from the network's
+// output and the diagonal (the values k_assemble writes), else P's values.
+template <bool K32, bool FROM_O>
+__global__ __launch_bounds__(256) void k_quad_pv(int n, int K, const int32_t *__restrict__ rp,
+                                                 const int32_t *__restrict__ ci,
+                                                 const float *__restrict__ pval,
+                                                 const float *__restrict__ O,
+                                                 const double *__restrict__ diag, int nx, int ny,
+                                                 const uint16_t *__restrict__ Vh,
+                                                 double *__restrict__ Y)
+{
+    const int q = threadIdx.x & 3;
+    for (int64_t i = (int64_t)xcd_block() * QROWS + (threadIdx.x >> 2); i < n;
+         i += (int64_t)gridDim.x * QROWS) {
+        const int beg = rp[i], end = rp[i + 1];
+        const RowPos rpos = row_pos(i, nx, ny);
+        const double dg = FROM_O ? diag[i] : 1.0;
+        double acc[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            acc[e] = 0.0;
+        for (int p0 = beg; p0 < end; p0 += 4) {
+            const int p = p0 + q;
+            const bool in = p < end;
+            const int c = in ? ci[p] : (int)i;
+            float a = 0.0f;
+            if constexpr (FROM_O) {
+                const int sl = in ? slot_at(rpos, i, c, nx, ny) : -1;
+                if (sl >= 0)
+                    a = (float)(((sl == CENTER ? 1.0 : 0.0) + (double)O[i * NO + sl]) / dg);
+            } else {
+                a = in ? pval[p] : 0.0f;
+            }
+            double v[4][8];
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                quad_v<K32>(Vh, quad_lane(c, t), K, q, v[t]);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const double at = (double)quad_lane(a, t);
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    acc[e] = fma(at, v[t][e], acc[e]);
+            }
+        }
+        if constexpr (K32) {
+#pragma unroll
+            for (int e = 0; e < 8; e += 2) {
+                f64x2 o = {acc[e], acc[e + 1]};
+                *(f64x2 *)(Y + i * 32 + q * 8 + e) = o;
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (q + 4 * e < K)
+                    Y[i * K + q + 4 * e] = acc[e];
+        }
+    }
+}
+
+// The row sum of val_p X[ci_p] over row i's entries (a quad's 8 values each)
+template <bool K32>
+__device__ __forceinline__ void quad_row(const int32_t *__restrict__ ci,
+                                         const double *__restrict__ val,
+                                         const double *__restrict__ X, int64_t i, int beg, int end,
+                                         int K, int q, double *acc)
+{
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        acc[e] = 0.0;
+    for (int p0 = beg; p0 < end; p0 += 4) {
+        const int p = p0 + q;
+        const bool in = p < end;
+        const int c = in ? ci[p] : (int)i;
+        const double a = in ? val[p] : 0.0;
+        double x[4][8];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            quad_x<K32>(X, quad_lane(c, t), K, q, x[t]);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const double at = quad_lane(a, t);
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                acc[e] = fma(at, x[t][e], acc[e]);
+        }
+    }
+}
+
+// R = A Y - V, and block partials of ||R||_F^2.
+template <bool K32>
+__global__ __launch_bounds__(256) void k_quad_residual(int n, int K,
+                                                       const int32_t *__restrict__ rp,
+                                                       const int32_t *__restrict__ ci,
+                                                       const double *__restrict__ val,
+                                                       const double *__restrict__ Y,
+                                                       const uint16_t *__restrict__ Vh,
+                                                       double *__restrict__ R,
+                                                       double *__restrict__ part)
+{
+    const int q = threadIdx.x & 3;
+    double ssq = 0.0;
+    for (int64_t i = (int64_t)xcd_block() * QROWS + (threadIdx.x >> 2); i < n;
+         i += (int64_t)gridDim.x * QROWS) {
+        double acc[8], v[8];
+        quad_row<K32>(ci, val, Y, i, rp[i], rp[i + 1], K, q, acc);
+        quad_v<K32>(Vh, i, K, q, v);
+        if constexpr (K32)
+            quad_transpose(v, q);                   // to the fp64 rows' order
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+            const f64x2 r = {acc[e] - v[e], acc[e + 1] - v[e + 1]};
+            ssq = fma(r.x, r.x, ssq);
+            ssq = fma(r.y, r.y, ssq);
+            if constexpr (K32) {
+                *(f64x2 *)(R + i * 32 + 4 * e + 2 * q) = r;
+            } else {
+                if (q + 4 * e < K)
+                    R[i * K + q + 4 * e] = r.x;
+                if (q + 4 * e + 4 < K)
+                    R[i * K + q + 4 * e + 4] = r.y;
+            }
+        }
+    }
+    double m = 0.0;
+    block_sum_max(ssq, m);
+    if (threadIdx.x == 0)
+        part[blockIdx.x] = ssq;
+}
+
+// G = scale A^T R on a row, then dP_e = sum_k G[i][k] v_k[c] for its entries:
+// dP (TO_O false), or dL/dO (n x 32 bf16) with dO_{i,slot} = bf16(dP_e / a_ii).
+template <bool K32, bool TO_O>
+__global__ __launch_bounds__(256) void k_quad_grad(int n, int K, const int32_t *__restrict__ rp,
+                                                   const int32_t *__restrict__ ci,
+                                                   const double *__restrict__ tval,
+                                                   const double *__restrict__ R, double scale,
+                                                   const uint16_t *__restrict__ Vh,
+                                                   double *__restrict__ dP,
+                                                   const double *__restrict__ diag, int nx, int ny,
+                                                   uint16_t *__restrict__ dO)
+{
+    __shared__ u32x4 lrow[TO_O ? QROWS : 1][NO / 8];      // a row's 32 bf16 values
+    const int q = threadIdx.x & 3, g = threadIdx.x >> 2;
+    for (int64_t i = (int64_t)xcd_block() * QROWS + g; i < n; i += (int64_t)gridDim.x * QROWS) {
+        const int beg = rp[i], end = rp[i + 1];
+        const RowPos rpos = row_pos(i, nx, ny);
+        const double dg = TO_O ? diag[i] : 1.0;
+        double gr[8];
+        quad_row<K32>(ci, tval, R, i, beg, end, K, q, gr);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            gr[e] *= scale;
+        if constexpr (K32)
+            quad_transpose(gr, q);                  // to the fp16 rows' order
+        if constexpr (TO_O) {
+            lrow[g][q] = u32x4{0u, 0u, 0u, 0u};
+            wave_sync();
+        }
+        for (int p0 = beg; p0 < end; p0 += 4) {
+            const int p = p0 + q;
+            const bool in = p < end;
+            const int c = in ? ci[p] : (int)i;
+            double mine = 0.0;
+            double v[4][8];
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                quad_v<K32>(Vh, quad_lane(c, t), K, q, v[t]);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                double s = 0.0;
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    s = fma(gr[e], v[t][e], s);
+                s += quad<QUAD_XOR1>(s);
+                s += quad<QUAD_XOR2>(s);
+                if (t == q)
+                    mine = s;
+            }
+            if constexpr (TO_O) {
+                const int sl = in ? slot_at(rpos, i, c, nx, ny) : -1;
+                if (sl >= 0)
+                    ((uint16_t *)lrow[g])[sl] = bf16_of_d(mine / dg);
+            } else if (in) {
+                dP[p] = mine;
+            }
+        }
+        if constexpr (TO_O) {
+            wave_sync();
+            *(u32x4 *)(dO + i * NO + q * 8) = lrow[g][q];
+            wave_sync();
         }
     }
 }
@@ -722,31 +960,71 @@ __global__ void k_loss_fold(const double *__restrict__ part, int nb, double scal
 }
 
 // ---------------------------------------------------------------------------
-// Backward pass.  Per 16-row tile: dH2^T = W3 dO^T and dH1^T = W2 dH2^T on
-// the MFMA units (masked by the ReLU, rounded to bf16), then the weight
-// gradients dW3 = H2^T dO, dW2 = H1^T dH2, dW1 = F^T dH1 as MFMA products
-// over the tile's rows (operands transposed through LDS), accumulated per
-// wave across tiles; bias gradients are column sums.  Each block writes its
-// NPARAM partial gradients; k_grad_fold sums blocks in order.
+// Backward pass.  Per 16-row tile, one wave: dH2^T = W3 dO^T and dH2 = dO W3^T
+// (the same values in two register layouts), dH1 = dH2 W2^T, masked by the
+// ReLU and rounded to bf16, then the weight gradients dW3 = H2^T dO, dW2 =
+// H1^T dH2 and dW1 = F^T dH1 over the tile's rows, accumulated per wave
+// across tiles; bias gradients are column sums.  Each block writes its NPARAM
+// partial gradients; k_grad_fold sums blocks in order.
+//
+// A product over rows needs its operands by column, four rows per lane.  The
+// result layout of dH2 and dH1 computed untransposed is that layout (lane l
+// holds rows 4 (l / 16) + r of column l mod 16), and for F, H1, H2 and dO a
+// lane loads 4 (or 2) consecutive columns of its four rows and packs them by
+// column, which makes column tile a the columns 4 j + a (2 j + a): a row is
+// one contiguous 128-byte read, and nothing goes through LDS but the weights.
+// Latency-bound with one wave per SIMD (160 accumulators a lane), so the next
+// tile's loads run under the current tile's 72 products: 386 us at 262,144
+// rows with the tile staged in LDS value by value, 65 us now (the fold of the
+// blocks' partials took 124 us with 512 of them in turn per parameter).
 // ---------------------------------------------------------------------------
 
+// operand 16 x 16 tiles of the weights, one 8-byte value per lane
 struct BackLds {
-    uint16_t w3[NH * NO];    // W3 as stored: [hidden 64][out 32]
-    uint16_t w2[NH * NH];    // W2 as stored: [in 64][out 64]
+    uint2 w3n[4][2][64];     // [h tile][o step]: W3[16 t + c][16 s + 4 g ..]
+    uint2 w3p[4][2][64];     // [h mod 4][o step]: W3[4 c + a][16 s + 4 g ..]
+    uint2 w2p[4][4][64];     // [in mod 4][h step]: W2[4 c + a][16 s + 4 g ..]
 };
 
-struct TileLds {             // one wave's 16-row tile, row-major
-    uint16_t f[16 * NF], h1[16 * NH], h2[16 * NH], dO[16 * NO], dh2[16 * NH], dh1[16 * NH];
-};
-
-__device__ __forceinline__ s16x4 col4(const uint16_t *t, int ld, int r0, int c)
+__device__ __forceinline__ s16x4 as_s16x4(uint2 v) { return __builtin_bit_cast(s16x4, v); }
+// the low (high) halves of two words
+__device__ __forceinline__ uint32_t lo16(uint32_t a, uint32_t b)
+{
+    return __builtin_amdgcn_perm(b, a, 0x05040100u);
+}
+__device__ __forceinline__ uint32_t hi16(uint32_t a, uint32_t b)
+{
+    return __builtin_amdgcn_perm(b, a, 0x07060302u);
+}
+// four rows of columns 4 c .. 4 c + 3, by column
+__device__ __forceinline__ void by_column(const uint2 (&x)[4], s16x4 (&op)[4])
+{
+    op[0] = as_s16x4(uint2{lo16(x[0].x, x[1].x), lo16(x[2].x, x[3].x)});
+    op[1] = as_s16x4(uint2{hi16(x[0].x, x[1].x), hi16(x[2].x, x[3].x)});
+    op[2] = as_s16x4(uint2{lo16(x[0].y, x[1].y), lo16(x[2].y, x[3].y)});
+    op[3] = as_s16x4(uint2{hi16(x[0].y, x[1].y), hi16(x[2].y, x[3].y)});
+}
+// bf16 of the gradient where the activation is positive, else 0
+__device__ __forceinline__ s16x4 masked_bf16(f32x4 c, s16x4 act)
 {
     s16x4 r;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-        r[q] = (short)t[(r0 + q) * ld + c];
+        r[q] = (short)bf16_of(f_of((uint16_t)act[q]) > 0.0f ? c[q] : 0.0f);
     return r;
 }
+__device__ __forceinline__ float sum4(s16x4 v)
+{
+    return (f_of((uint16_t)v[0]) + f_of((uint16_t)v[1])) +
+           (f_of((uint16_t)v[2]) + f_of((uint16_t)v[3]));
+}
+
+// one tile's inputs as a lane loads them
+struct TileIn {
+    uint2 f[4], h1[4], h2[4];     // rows 4 g + t, columns 4 c ..
+    uint32_t dO[4];               // rows 4 g + t, columns 2 c, 2 c + 1
+    uint2 dOr[2], h2r[4];         // row c, columns 16 s + 4 g ..
+};
 
 __global__ __launch_bounds__(256) void k_backward(int n, const uint16_t *__restrict__ feat,
                                                   const uint16_t *__restrict__ H1,
@@ -755,191 +1033,176 @@ __global__ __launch_bounds__(256) void k_backward(int n, const uint16_t *__restr
                                                   const uint16_t *__restrict__ wq,
                                                   float *__restrict__ part)
 {
-    __shared__ BackLds W;
-    __shared__ TileLds T[4];
-    __shared__ float red[4][NPARAM / 4 + 1];   // wave-level staging of one quarter
-    for (int e = threadIdx.x; e < NH * NO; e += blockDim.x)
-        W.w3[e] = wq[QW3 + e];
-    for (int e = threadIdx.x; e < NH * NH; e += blockDim.x)
-        W.w2[e] = wq[QW2 + e];
-    __syncthreads();
+    __shared__ union {
+        BackLds w;
+        float red[NPARAM];
+    } L;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    const int col = lane & 15, kq = (lane >> 4) * 4;
-    TileLds &t = T[wave];
-    f32x4 gw3[4][2], gw2[4][4], gw1[NF / 16][4];   // [row tile of W][col tile of W]
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-            gw3[a][b] = f32x4{0, 0, 0, 0};
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-            gw2[a][b] = f32x4{0, 0, 0, 0};
-#pragma unroll
-    for (int a = 0; a < NF / 16; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-            gw1[a][b] = f32x4{0, 0, 0, 0};
-    float gb1 = 0.0f, gb2 = 0.0f, gb3 = 0.0f;   // lane c: column c
-    const int64_t ntile = ((int64_t)n + 15) / 16;
-    for (int64_t tile = (int64_t)blockIdx.x * nw + wave; tile < ntile;
-         tile += (int64_t)gridDim.x * nw) {
-        const int64_t r0 = tile * 16;
-        // stage the tile's inputs (rows beyond n read as 0)
-        for (int e = lane; e < 16 * NF; e += 64) {
-            const int64_t r = r0 + e / NF;
-            t.f[e] = r < n ? feat[r * NF + e % NF] : 0;
-        }
-        for (int e = lane; e < 16 * NO; e += 64) {
-            const int64_t r = r0 + e / NO;
-            t.dO[e] = r < n ? dO[r * NO + e % NO] : 0;
-        }
-        for (int e = lane; e < 16 * NH; e += 64) {
-            const int64_t r = r0 + e / NH;
-            t.h1[e] = r < n ? H1[r * NH + e % NH] : 0;
-            t.h2[e] = r < n ? H2[r * NH + e % NH] : 0;
-        }
-        __builtin_amdgcn_wave_barrier();
-        // B operand dO^T: lane holds dO[row col][o = ks*16 + kq .. +3]
-        s16x4 ob[2];
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-            ob[ks] = lds4(&t.dO[col * NO + ks * 16 + kq]);
-        // dH2^T (64 x 16) = W3 (64 x 32) dO^T; mask, bf16, keep and stage
-        s16x4 dh2[4];
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) {
-            f32x4 c = {0, 0, 0, 0};
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks)
-                c = mfma(lds4(&W.w3[(ot * 16 + col) * NO + ks * 16 + kq]), ob[ks], c);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int h = ot * 16 + kq + q;
-                const float m = f_of(t.h2[col * NH + h]) > 0.0f ? c[q] : 0.0f;
-                dh2[ot][q] = (short)bf16_of(m);
-                t.dh2[col * NH + h] = (uint16_t)dh2[ot][q];
-            }
-        }
-        // dH1^T (64 x 16) = W2 (64 x 64) dH2^T; mask, bf16, stage
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) {
-            f32x4 c = {0, 0, 0, 0};
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-                c = mfma(lds4(&W.w2[(ot * 16 + col) * NH + ks * 16 + kq]), dh2[ks], c);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int h = ot * 16 + kq + q;
-                const float m = f_of(t.h1[col * NH + h]) > 0.0f ? c[q] : 0.0f;
-                t.dh1[col * NH + h] = bf16_of(m);
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        // weight gradients over the tile's 16 rows: D (M x N) += A (M x 16 rows)
-        // B (16 rows x N), A[i][k] = X[row k][i], B[k][j] = Y[row k][j]
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-                gw3[a][b] = mfma(col4(t.h2, NH, kq, a * 16 + col), col4(t.dO, NO, kq, b * 16 + col),
-                                 gw3[a][b]);
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-                gw2[a][b] = mfma(col4(t.h1, NH, kq, a * 16 + col),
-                                 col4(t.dh2, NH, kq, b * 16 + col), gw2[a][b]);
-#pragma unroll
-        for (int a = 0; a < NF / 16; ++a)
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-                gw1[a][b] = mfma(col4(t.f, NF, kq, a * 16 + col),
-                                 col4(t.dh1, NH, kq, b * 16 + col), gw1[a][b]);
-        // bias gradients: column sums of dO, dH2, dH1 over the tile (lane c
-        // owns columns c, c+64 of each)
-        for (int q = 0; q < 16; ++q) {
-            if (lane < NO)
-                gb3 += f_of(t.dO[q * NO + lane]);
-            gb2 += f_of(t.dh2[q * NH + lane]);
-            gb1 += f_of(t.dh1[q * NH + lane]);
-        }
-        __builtin_amdgcn_wave_barrier();
+    const int c = lane & 15, g = lane >> 4;
+    const uint16_t *w3 = wq + QW3, *w2 = wq + QW2;
+    for (int e = wave; e < 8; e += nw) {
+        const int t = e >> 1, s = e & 1;
+        L.w.w3n[t][s][lane] = *(const uint2 *)(w3 + (16 * t + c) * NO + 16 * s + 4 * g);
+        L.w.w3p[t][s][lane] = *(const uint2 *)(w3 + (4 * c + t) * NO + 16 * s + 4 * g);
     }
-    // per-block partials in parameter order, folded over the 4 waves in LDS
-    // (fixed wave order) one quarter of the parameters at a time
-    auto emit = [&](int q0, int q1) {
-        // each wave writes its sums for the parameters in [q0, q1): every
-        // parameter is held by exactly one lane of every wave
-        float *mine = red[wave];
-        // gw3: D[i][j] with i = hidden (a*16 + 4(l/16)+r), j = out (b*16 + col)
+    for (int e = wave; e < 16; e += nw) {
+        const int t = e >> 2, s = e & 3;
+        L.w.w2p[t][s][lane] = *(const uint2 *)(w2 + (4 * c + t) * NH + 16 * s + 4 * g);
+    }
+    __syncthreads();
+    f32x4 gw3[4][2], gw2[4][4], gw1[4][4];      // [row tile of W][column tile of W]
+    float gb1[4], gb2[4], gb3[2];
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < 4; ++a) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            gw2[a][b] = f32x4{0, 0, 0, 0};
+            gw1[a][b] = f32x4{0, 0, 0, 0};
+            gw3[a][b & 1] = f32x4{0, 0, 0, 0};
+        }
+        gb1[a] = gb2[a] = gb3[a & 1] = 0.0f;
+    }
+    const int64_t ntile = ((int64_t)n + 15) / 16, step = (int64_t)gridDim.x * nw;
+    // rows >= n read row n - 1 and a zero dO, which zeroes all they add
+    auto load = [&](int64_t tile, TileIn &x) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int64_t r = tile * 16 + 4 * g + t, rc = min(r, (int64_t)n - 1);
+            x.f[t] = *(const uint2 *)(feat + rc * NF + 4 * c);
+            x.h1[t] = *(const uint2 *)(H1 + rc * NH + 4 * c);
+            x.h2[t] = *(const uint2 *)(H2 + rc * NH + 4 * c);
+            x.dO[t] = r < n ? *(const uint32_t *)(dO + rc * NO + 2 * c) : 0u;
+        }
+        const int64_t r = tile * 16 + c, rc = min(r, (int64_t)n - 1);
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+            x.dOr[s] = r < n ? *(const uint2 *)(dO + rc * NO + 16 * s + 4 * g) : uint2{0u, 0u};
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            x.h2r[t] = *(const uint2 *)(H2 + rc * NH + 16 * t + 4 * g);
+    };
+    int64_t tile = (int64_t)blockIdx.x * nw + wave;
+    TileIn cur;
+    if (tile < ntile)
+        load(tile, cur);
+    for (; tile < ntile; tile += step) {
+        TileIn nxt;
+        load(min(tile + step, ntile - 1), nxt);
+        __builtin_amdgcn_sched_barrier(0);
+        const s16x4 ob[2] = {as_s16x4(cur.dOr[0]), as_s16x4(cur.dOr[1])};
+        s16x4 fc[4], h1c[4], h2c[4], oc[2];
+        by_column(cur.f, fc);
+        by_column(cur.h1, h1c);
+        by_column(cur.h2, h2c);
+        oc[0] = as_s16x4(uint2{lo16(cur.dO[0], cur.dO[1]), lo16(cur.dO[2], cur.dO[3])});
+        oc[1] = as_s16x4(uint2{hi16(cur.dO[0], cur.dO[1]), hi16(cur.dO[2], cur.dO[3])});
+        s16x4 d2t[4], d2[4], d1[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            f32x4 x = {0, 0, 0, 0}, y = {0, 0, 0, 0};
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                x = mfma(as_s16x4(L.w.w3n[t][s][lane]), ob[s], x);
+                y = mfma(ob[s], as_s16x4(L.w.w3p[t][s][lane]), y);
+            }
+            d2t[t] = masked_bf16(x, as_s16x4(cur.h2r[t]));
+            d2[t] = masked_bf16(y, h2c[t]);
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            f32x4 x = {0, 0, 0, 0};
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                x = mfma(d2t[s], as_s16x4(L.w.w2p[t][s][lane]), x);
+            d1[t] = masked_bf16(x, h1c[t]);
+        }
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
 #pragma unroll
             for (int b = 0; b < 2; ++b)
+                gw3[a][b] = mfma(h2c[a], oc[b], gw3[a][b]);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int e = OW3 + (a * 16 + kq + r) * NO + b * 16 + col;
-                    if (e >= q0 && e < q1)
-                        mine[e - q0] = gw3[a][b][r];
-                }
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int e = OW2 + (a * 16 + kq + r) * NH + b * 16 + col;
-                    if (e >= q0 && e < q1)
-                        mine[e - q0] = gw2[a][b][r];
-                }
-#pragma unroll
-        for (int a = 0; a < NF / 16; ++a)
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int e = OW1 + (a * 16 + kq + r) * NH + b * 16 + col;
-                    if (e >= q0 && e < q1)
-                        mine[e - q0] = gw1[a][b][r];
-                }
-        {
-            int e = OB3 + lane;
-            if (lane < NO && e >= q0 && e < q1)
-                mine[e - q0] = gb3;
-            e = OB2 + lane;
-            if (e >= q0 && e < q1)
-                mine[e - q0] = gb2;
-            e = OB1 + lane;
-            if (e >= q0 && e < q1)
-                mine[e - q0] = gb1;
+            for (int b = 0; b < 4; ++b) {
+                gw2[a][b] = mfma(h1c[a], d2[b], gw2[a][b]);
+                gw1[a][b] = mfma(fc[a], d1[b], gw1[a][b]);
+            }
+            gb2[a] += sum4(d2[a]);
+            gb1[a] += sum4(d1[a]);
         }
-        __syncthreads();
-        for (int e = threadIdx.x; e < q1 - q0; e += blockDim.x) {
-            float s = red[0][e];
-            for (int w = 1; w < nw; ++w)
-                s += red[w][e];
-            part[(size_t)blockIdx.x * NPARAM + q0 + e] = s;
-        }
-        __syncthreads();
+        gb3[0] += sum4(oc[0]);
+        gb3[1] += sum4(oc[1]);
+        cur = nxt;
+    }
+    // the four row groups of a column
+    auto groups = [](float v) {
+        v += __shfl_xor(v, 16);
+        return v + __shfl_xor(v, 32);
     };
-    constexpr int QS = NPARAM / 4;
-    emit(0, QS);
-    emit(QS, 2 * QS);
-    emit(2 * QS, 3 * QS);
-    emit(3 * QS, NPARAM);
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        gb1[a] = groups(gb1[a]);
+        gb2[a] = groups(gb2[a]);
+    }
+    gb3[0] = groups(gb3[0]);
+    gb3[1] = groups(gb3[1]);
+    // the block's sums in parameter order, the waves in turn; every parameter
+    // is held by exactly one lane of a wave (the biases by g = 0)
+    __syncthreads();                            // the weights are done with
+    for (int w = 0; w < nw; ++w) {
+        if (w == wave) {
+            auto add = [&](int e, float v) { L.red[e] = w == 0 ? v : L.red[e] + v; };
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = 4 * (4 * g + r) + a;
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+                        add(OW3 + row * NO + 2 * c + b, gw3[a][b][r]);
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) {
+                        add(OW2 + row * NH + 4 * c + b, gw2[a][b][r]);
+                        add(OW1 + row * NH + 4 * c + b, gw1[a][b][r]);
+                    }
+                }
+            if (g == 0) {
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    add(OB2 + 4 * c + a, gb2[a]);
+                    add(OB1 + 4 * c + a, gb1[a]);
+                }
+                add(OB3 + 2 * c, gb3[0]);
+                add(OB3 + 2 * c + 1, gb3[1]);
+            }
+        }
+        __syncthreads();
+    }
+    for (int e = threadIdx.x; e < NPARAM; e += blockDim.x)
+        part[(size_t)blockIdx.x * NPARAM + e] = L.red[e];
 }
 
-// grad[e] (+)= sum over blocks of part[b][e] (fixed block order, fp64).
-__global__ void k_grad_fold(const float *__restrict__ part, int nb, int accumulate,
-                            double *__restrict__ grad)
+// grad[e] (+)= sum over blocks of part[b][e] in fp64: 32 parameters per block,
+// eight runs of consecutive blocks each, the runs' sums added in order.
+constexpr int FOLD_E = 32, FOLD_RUNS = 8;
+__global__ __launch_bounds__(256) void k_grad_fold(const float *__restrict__ part, int nb,
+                                                   int accumulate, double *__restrict__ grad)
 {
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < NPARAM; e += gridDim.x * blockDim.x) {
-        double s = 0.0;
-        for (int b = 0; b < nb; ++b)
+    __shared__ double ls[FOLD_RUNS][FOLD_E];
+    const int le = threadIdx.x & (FOLD_E - 1), run = threadIdx.x / FOLD_E;
+    const int e = blockIdx.x * FOLD_E + le;
+    const int len = (nb + FOLD_RUNS - 1) / FOLD_RUNS, lo = run * len, hi = min(lo + len, nb);
+    double s = 0.0;
+    if (e < NPARAM) {
+#pragma unroll 8
+        for (int b = lo; b < hi; ++b)
             s += (double)part[(size_t)b * NPARAM + e];
+    }
+    ls[run][le] = s;
+    __syncthreads();
+    if (run == 0 && e < NPARAM) {
+#pragma unroll
+        for (int r = 1; r < FOLD_RUNS; ++r)
+            s += ls[r][le];
         grad[e] = (accumulate ? grad[e] : 0.0) + s;
     }
 }
@@ -1050,7 +1313,7 @@ namespace {
 
 constexpr size_t SALIGN = 256;
 constexpr int MAXB_ROW = 4096;     // grid cap of the row-parallel kernels
-constexpr int MAXB_BACK = 512;     // grid cap of the backward pass (partials)
+constexpr int MAXB_BACK = 256;     // grid cap of the backward pass: a block per CU (partials)
 
 size_t salign(size_t x) { return (x + SALIGN - 1) / SALIGN * SALIGN; }
 
@@ -1190,27 +1453,53 @@ int read_flag(unsigned *bad, hipStream_t s, unsigned *out)
 void enqueue_forward(int64_t n, const uint16_t *feat, const uint16_t *w, const float *prm, float *O,
                      uint16_t *h1, uint16_t *h2, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_forward, dim3(tile_grid(n, 2048)), dim3(256), 0, s, (int)n, feat, w, prm,
+    // two blocks per CU: what its registers allow; more only stage the
+    // weights again (262,144 rows in 2048 blocks: 99 us, 512: 53 us)
+    hipLaunchKernelGGL(k_forward, dim3(tile_grid(n, 512)), dim3(256), 0, s, (int)n, feat, w, prm,
                        O, h1, h2);
 }
 
-int enqueue_grad_p(const cbg_csr *A, const double *tval, const float *pval, int K,
-                   const uint16_t *V, double scale, double *loss, int accumulate, double *dP,
-                   const SpaiWs &W, hipStream_t s)
+// Loss and gradient of one matrix: with O (the network's output; grid and the
+// diagonal in W.diag set) P comes from it and the gradient goes to dO, else P
+// is pval and the gradient dP.
+template <bool K32>
+void enqueue_loss(const cbg_csr *A, const double *tval, const float *pval, const float *O,
+                  const int32_t grid[3], int K, const uint16_t *V, double scale, double *loss,
+                  int accumulate, double *dP, uint16_t *dO, const SpaiWs &W, hipStream_t s)
 {
-    const int gb = group_grid(A->n);
-    hipLaunchKernelGGL(k_spmm<MM_PV>, dim3(gb), dim3(256), 0, s, A->n, K, A->row_ptr, A->col_idx,
-                       A->val, pval, (const double *)nullptr, V, W.X0, 1.0, (double *)nullptr);
-    hipLaunchKernelGGL(k_spmm<MM_AY_MINUS_V>, dim3(gb), dim3(256), 0, s, A->n, K, A->row_ptr,
-                       A->col_idx, A->val, (const float *)nullptr, (const double *)W.X0, V, W.X1,
-                       1.0, W.lpart);
+    const int gb = (int)std::min<int64_t>(std::max<int64_t>(((int64_t)A->n + QROWS - 1) / QROWS, 1),
+                                          MAXB_ROW);
+    const int nx = O ? grid[0] : 1, ny = O ? grid[1] : 1;
+    const double *diag = W.diag;
+    if (O)
+        hipLaunchKernelGGL((k_quad_pv<K32, true>), dim3(gb), dim3(256), 0, s, A->n, K, A->row_ptr,
+                           A->col_idx, pval, O, diag, nx, ny, V, W.X0);
+    else
+        hipLaunchKernelGGL((k_quad_pv<K32, false>), dim3(gb), dim3(256), 0, s, A->n, K,
+                           A->row_ptr, A->col_idx, pval, O, diag, nx, ny, V, W.X0);
+    hipLaunchKernelGGL((k_quad_residual<K32>), dim3(gb), dim3(256), 0, s, A->n, K, A->row_ptr,
+                       A->col_idx, A->val, (const double *)W.X0, V, W.X1, W.lpart);
     hipLaunchKernelGGL(k_loss_fold, dim3(1), dim3(256), 0, s, (const double *)W.lpart, gb, scale,
                        accumulate, loss);
-    hipLaunchKernelGGL(k_spmm<MM_ATR>, dim3(gb), dim3(256), 0, s, A->n, K, A->row_ptr, A->col_idx,
-                       tval, (const float *)nullptr, (const double *)W.X1, V, W.X0, 2.0 * scale,
-                       (double *)nullptr);
-    hipLaunchKernelGGL(k_sddmm, dim3(gb), dim3(256), 0, s, A->n, K, A->row_ptr, A->col_idx,
-                       (const double *)W.X0, V, dP);
+    if (O)
+        hipLaunchKernelGGL((k_quad_grad<K32, true>), dim3(gb), dim3(256), 0, s, A->n, K,
+                           A->row_ptr, A->col_idx, tval, (const double *)W.X1, 2.0 * scale, V, dP,
+                           diag, nx, ny, dO);
+    else
+        hipLaunchKernelGGL((k_quad_grad<K32, false>), dim3(gb), dim3(256), 0, s, A->n, K,
+                           A->row_ptr, A->col_idx, tval, (const double *)W.X1, 2.0 * scale, V, dP,
+                           diag, nx, ny, dO);
+}
+
+int enqueue_grad(const cbg_csr *A, const double *tval, const float *pval, const float *O,
+                 const int32_t grid[3], int K, const uint16_t *V, double scale, double *loss,
+                 int accumulate, double *dP, uint16_t *dO, const SpaiWs &W, hipStream_t s)
+{
+    // the 16-byte loads of the K = 32 form: V comes from the caller
+    if (K == 32 && a16(V))
+        enqueue_loss<true>(A, tval, pval, O, grid, K, V, scale, loss, accumulate, dP, dO, W, s);
+    else
+        enqueue_loss<false>(A, tval, pval, O, grid, K, V, scale, loss, accumulate, dP, dO, W, s);
     SP_TRY(hipGetLastError());
     return CBG_OK;
 }
@@ -1222,7 +1511,7 @@ int enqueue_backward(int64_t n, const uint16_t *feat, const uint16_t *h1, const 
     const int nb = tile_grid(n, MAXB_BACK);
     hipLaunchKernelGGL(k_backward, dim3(nb), dim3(256), 0, s, (int)n, feat, h1, h2, dO, w,
                        W.gpart);
-    hipLaunchKernelGGL(k_grad_fold, dim3((NPARAM + 255) / 256), dim3(256), 0, s,
+    hipLaunchKernelGGL(k_grad_fold, dim3((NPARAM + FOLD_E - 1) / FOLD_E), dim3(256), 0, s,
                        (const float *)W.gpart, nb, accumulate, grad);
     SP_TRY(hipGetLastError());
     return CBG_OK;
@@ -1437,7 +1726,8 @@ int cbg_spai_grad_p(const cbg_csr *A, const double *t_val, const float *p_val, i
         return e;
     hipStream_t s = (hipStream_t)stream;
     SpaiWs W = carve_spai(ws, A->n, A->nnz, K, nullptr);
-    return enqueue_grad_p(A, t_val, p_val, K, V, scale, loss, accumulate, dP, W, s);
+    return enqueue_grad(A, t_val, p_val, nullptr, nullptr, K, V, scale, loss, accumulate, dP,
+                        nullptr, W, s);
 }
 
 int cbg_spai_grad_o(const cbg_csr *A, const int32_t grid[3], const double *dP, uint16_t *dO,
@@ -1463,8 +1753,23 @@ int cbg_mlp_backward(int32_t n, const uint16_t *feat, const uint16_t *h1, const 
     if (e)
         return e;
     SpaiWs W = carve_spai(ws, n, 0, 0, nullptr);
-    return enqueue_backward(n, feat, h1, h2, dO, weights, grad, accumulate, W,
-                            (hipStream_t)stream);
+    hipStream_t s = (hipStream_t)stream;
+    // the kernel's 8-byte loads: an input that is not so aligned is read from a
+    // copy in the workspace
+    auto aligned = [&](const uint16_t *&p, void *copy, size_t count) {
+        if (((uintptr_t)p & 7u) == 0)
+            return hipSuccess;
+        const hipError_t r = hipMemcpyAsync(copy, p, 2 * count, hipMemcpyDeviceToDevice, s);
+        p = (const uint16_t *)copy;
+        return r;
+    };
+    static_assert(sizeof(double) * MAXB_ROW >= 2 * NWBF, "the weights' copy fits the loss partials");
+    SP_TRY(aligned(feat, W.feat, (size_t)n * NF));
+    SP_TRY(aligned(h1, W.h1, (size_t)n * NH));
+    SP_TRY(aligned(h2, W.h2, (size_t)n * NH));
+    SP_TRY(aligned(dO, W.dO, (size_t)n * NO));
+    SP_TRY(aligned(weights, W.lpart, NWBF));
+    return enqueue_backward(n, feat, h1, h2, dO, weights, grad, accumulate, W, s);
 }
 
 int cbg_spai_loss_grad(const cbg_csr *A, const double *t_val, const int32_t grid[3],
@@ -1484,18 +1789,16 @@ int cbg_spai_loss_grad(const cbg_csr *A, const double *t_val, const int32_t grid
     if (A->n == 0) {
         hipLaunchKernelGGL(k_loss_fold, dim3(1), dim3(256), 0, s, (const double *)W.lpart, 0, 0.0,
                            accumulate, loss);
-        hipLaunchKernelGGL(k_grad_fold, dim3((NPARAM + 255) / 256), dim3(256), 0, s,
+        hipLaunchKernelGGL(k_grad_fold, dim3((NPARAM + FOLD_E - 1) / FOLD_E), dim3(256), 0, s,
                            (const float *)W.gpart, 0, accumulate, grad);
         SP_TRY(hipGetLastError());
         return CBG_OK;
     }
     enqueue_forward(A->n, feat, weights, params, W.O, W.h1, W.h2, s);
-    hipLaunchKernelGGL(k_assemble, dim3(group_grid(A->n)), dim3(256), 0, s, A->n, A->row_ptr,
-                       A->col_idx, A->val, grid[0], grid[1], (const float *)W.O, W.pval);
-    if ((e = enqueue_grad_p(A, t_val, W.pval, K, V, scale, loss, accumulate, W.dP, W, s)))
+    enqueue_diag(A, W.diag, s);
+    if ((e = enqueue_grad(A, t_val, nullptr, W.O, grid, K, V, scale, loss, accumulate, nullptr,
+                          W.dO, W, s)))
         return e;
-    hipLaunchKernelGGL(k_grad_o, dim3(group_grid(A->n)), dim3(256), 0, s, A->n, A->row_ptr,
-                       A->col_idx, A->val, grid[0], grid[1], (const double *)W.dP, W.dO);
     return enqueue_backward(A->n, feat, W.h1, W.h2, W.dO, weights, grad, accumulate, W, s);
 }
 
