@@ -131,9 +131,10 @@ int launch_mgs(int fmt, const void *V, int64_t ld, const double *scales, int n, 
 bool fused_takes(int fmt, int64_t ld, int j);
 void launch_reduce(const RedWs &ws, int role, int nb_orth, int nb_spmv, int j, DevState *st,
                    const void *sa, double *out, int fmt, hipStream_t s);
-void launch_normalize(int fmt, const double *w, int n, int64_t nst, double *v_out, void *Q,
-                      const double *scale_slot, const double *tptr, double tval,
-                      const DevState *st, int check_done, hipStream_t s);
+// q = enc(v); reads the scale of a scaled format from its slot, writes the
+// scale 1 of the others
+void launch_encode(int fmt, const double *v, int n, void *Q, double *scale_slot, hipStream_t s);
+bool format_scaled(int fmt);
 // steps 13-14 as a pass: v = w / t stored through the accessor, z = v, or
 // dinv .* v when dinv is given; skipped once the cycle is done
 void launch_step_normalize(int fmt, const double *w, int n, int64_t ld, const double *dinv,

@@ -941,11 +941,16 @@ int cbg_encode(int32_t format, const double *v, int32_t n, void *q, double *scal
     if (!kernel_ws_ok(ws, ws_bytes, 0))
         return CBG_E_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
-    RedWs r = kernel_red(ws, 0);
-    const int g = launch_norm(v, n, r, s);
-    launch_reduce(r, RR_SCALE, 0, g, 0, nullptr, nullptr, scale, format, s);
-    if (n > 0)
-        launch_normalize(format, v, n, n, nullptr, q, scale, nullptr, 1.0, nullptr, 0, s);
+    if (format_scaled(format)) {
+        RedWs r = kernel_red(ws, 0);
+        const int g = launch_norm(v, n, r, s);
+        launch_reduce(r, RR_SCALE, 0, g, 0, nullptr, nullptr, scale, format, s);
+        if (n == 0) {
+            HIP_TRY(hipGetLastError());
+            return CBG_OK;
+        }
+    }
+    launch_encode(format, v, n, q, scale, s);
     HIP_TRY(hipGetLastError());
     return CBG_OK;
 }
