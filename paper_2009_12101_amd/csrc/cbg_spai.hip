@@ -245,80 +245,150 @@ __global__ __launch_bounds__(256) void k_features(int n, const int32_t *__restri
     }
 }
 
-// The same features from A's sliced-ELL copy with one-byte diagonal indices
-// (the same values and bits): one wave per 64-row slice, lane = row.  The
-// copy keeps each row's entries in CSR order, so the lane adds the
-// off-diagonal sum in that order; entries past the row's CSR length are
-// padding and skipped.  A batch's values and indices are loaded together
-// (indices clamped into the slice), then the neighbours' diagonals.  Each
-// lane assembles its row's 64 features in an LDS row of its own (odd word
-// stride: the 64 rows sit in distinct banks); the wave then writes two rows
-// per store.
+// The features of a 64-row slice of A's sliced-ELL copy with one-byte
+// diagonal indices (the same values and bits): one wave, lane = row, the
+// row's 64 features assembled in an LDS row of its own (odd word stride: the
+// 64 rows sit in distinct banks).  The copy keeps each row's entries in CSR
+// order, so the lane adds the off-diagonal sum in that order; entries past
+// the row's CSR length are padding and skipped.  A batch's values and indices
+// are loaded together (indices clamped into the slice), then the neighbours'
+// diagonals.  Returns the slots the row stores, one bit each.
 constexpr int FS_LD = NF / 2 + 1;       // LDS row stride in 32-bit words
 
-__global__ __launch_bounds__(256) void k_features_sell(
-    int n, int64_t nslice, const int32_t *__restrict__ rp, const int64_t *__restrict__ sp,
-    const uint8_t *__restrict__ sd, const double *__restrict__ sv,
-    const int32_t *__restrict__ sdiag, int ndiag, int nx, int ny,
-    const double *__restrict__ diag, uint16_t *__restrict__ feat, unsigned *__restrict__ bad)
+struct SellDix {
+    int n, ndiag, nx, ny;
+    int64_t nslice;
+    const int32_t *rp;
+    const int64_t *sp;
+    const uint8_t *sd;
+    const double *sv;
+    const int32_t *sdiag;
+};
+
+// What a diagonal says of its entries without their row: the offset col - row
+// and, on grids with nx, ny >= 3, where it fixes the triple (see slot_at), the
+// slot with dx + 1 and dy + 1 in bits 8 and 10 (-1: no stencil offset).
+struct DiagSlot {
+    int32_t off, code;
+};
+__device__ __forceinline__ void stage_diags(DiagSlot *t, const SellDix &A)
 {
-    __shared__ int32_t ldg[CBG_SELL_MAX_DIAG];
+    for (int k = threadIdx.x; k < A.ndiag; k += blockDim.x) {
+        const int32_t d = A.sdiag[k];
+        int code = -1;
+        if (A.nx >= 3 && A.ny >= 3) {
+            const int64_t S = (int64_t)A.nx * A.ny, zb = S - A.nx - 1;
+            const int64_t dz = d >= zb ? 1 : (d <= -zb ? -1 : 0), rem = d - dz * S;
+            const int64_t dy = rem >= A.nx - 1 ? 1 : (rem <= -(A.nx - 1) ? -1 : 0);
+            const int64_t dx = rem - dy * A.nx;
+            if (dx >= -1 && dx <= 1)
+                code = (int)((dz + 1) * 9 + (dy + 1) * 3 + (dx + 1)) | (int)(dx + 1) << 8 |
+                       (int)(dy + 1) << 10;
+        }
+        t[k] = {d, code};
+    }
+}
+
+// bf16(fl32(a / d)) with r = fl64(1 / d): a r is within two ulps of a / d, so
+// its fl32 is within one of the quotient's, and both round to the same bf16
+// unless the fl32's low half is within one of the midpoint 0x8000; then (and
+// with !fast: d so small or large that 1 / d loses bits) the division decides.
+__device__ __forceinline__ uint16_t bf16_ratio(double a, double d, double r, bool fast)
+{
+    float f = (float)(a * r);
+    const uint32_t low = __float_as_uint(f) & 0xFFFFu;
+    if (!fast || low - 0x7FFFu <= 2u)
+        f = (float)(a / d);
+    return bf16_of(f);
+}
+
+__device__ __forceinline__ uint32_t slice_features(const SellDix &A, int64_t sl,
+                                                   const DiagSlot *ldg,
+                                                   const double *__restrict__ diag, uint32_t *my,
+                                                   unsigned *__restrict__ bad)
+{
+    const int lane = threadIdx.x & 63;
+    uint16_t *myh = (uint16_t *)my;
+    const int64_t i = sl * 64 + lane;
+    const bool live = i < A.n;
+    const int64_t ic = live ? i : (int64_t)A.n - 1;
+    for (int q = 0; q < NF / 2; ++q)
+        my[q] = 0u;
+    const int64_t beg = A.sp[sl];
+    const int width = (int)((A.sp[sl + 1] - beg) / 64);
+    const int len = live ? A.rp[i + 1] - A.rp[i] : 0;
+    const double d = diag[ic];
+    const RowPos rpos = row_pos(ic, A.nx, A.ny);
+    const double r = 1.0 / d;
+    const bool fast = fabs(d) >= 0x1p-500 && fabs(d) <= 0x1p500;
+    const bool table = A.nx >= 3 && A.ny >= 3;
+    const int xin = 2 | (rpos.x > 0 ? 1 : 0) | (rpos.x < A.nx - 1 ? 4 : 0);
+    const int yin = 2 | (rpos.y > 0 ? 1 : 0) | (rpos.y < A.ny - 1 ? 4 : 0);
+    double off = 0.0;
+    uint32_t slots = 0u;
+    for (int k0 = 0; k0 < width; k0 += SL_B) {
+        double a[SL_B];
+        int32_t c[SL_B], code[SL_B];
+#pragma unroll
+        for (int u = 0; u < SL_B; ++u) {
+            const int64_t e = beg + (int64_t)min(k0 + u, width - 1) * 64 + lane;
+            a[u] = A.sv[e];
+            const DiagSlot ds = ldg[A.sd[e]];
+            c[u] = (int32_t)ic + ds.off;
+            code[u] = ds.code;
+        }
+        double dc[SL_B];
+#pragma unroll
+        for (int u = 0; u < SL_B; ++u)
+            dc[u] = diag[min(max(c[u], 0), A.n - 1)];
+#pragma unroll
+        for (int u = 0; u < SL_B; ++u) {
+            if (k0 + u >= len)
+                continue;
+            if (c[u] != (int32_t)ic)
+                off += fabs(a[u]);
+            int s = -1;
+            if (!table)
+                s = slot_at(rpos, ic, c[u], A.nx, A.ny);
+            else if (code[u] >= 0 && ((xin >> ((code[u] >> 8) & 3)) & (yin >> (code[u] >> 10)) & 1))
+                s = code[u] & 31;
+            if (s >= 0) {
+                slots |= 1u << s;
+                myh[s] = bf16_ratio(a[u], d, r, fast);
+                myh[NBR + s] = bf16_ratio(dc[u], d, r, fast);
+            }
+        }
+    }
+    if (live) {
+        const double margin = (d - off) / d;
+        if (!(d != 0.0) || !isfinite(margin))
+            *bad = 1u;
+        myh[27] = bf16_of((float)margin);
+    }
+    return slots;
+}
+
+// The slice's features out to memory, two rows per store, and (slots not
+// null) the slots each row stores.
+__global__ __launch_bounds__(256) void k_features_sell(SellDix A, const double *__restrict__ diag,
+                                                       uint16_t *__restrict__ feat,
+                                                       uint32_t *__restrict__ slots,
+                                                       unsigned *__restrict__ bad)
+{
+    __shared__ DiagSlot ldg[CBG_SELL_MAX_DIAG];
     __shared__ uint32_t lf[4][64 * FS_LD];
-    for (int t = threadIdx.x; t < ndiag; t += blockDim.x)
-        ldg[t] = sdiag[t];
+    stage_diags(ldg, A);
     __syncthreads();
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    uint32_t *my = lf[wv] + lane * FS_LD;
-    uint16_t *myh = (uint16_t *)my;
-    for (int64_t sl = (int64_t)blockIdx.x * 4 + wv; sl < nslice; sl += (int64_t)gridDim.x * 4) {
-        const int64_t i = sl * 64 + lane;
-        const bool live = i < n;
-        const int64_t ic = live ? i : (int64_t)n - 1;
-        for (int q = 0; q < NF / 2; ++q)
-            my[q] = 0u;
-        const int64_t beg = sp[sl];
-        const int width = (int)((sp[sl + 1] - beg) / 64);
-        const int len = live ? rp[i + 1] - rp[i] : 0;
-        const double d = diag[ic];
-        const RowPos rpos = row_pos(ic, nx, ny);
-        double off = 0.0;
-        for (int k0 = 0; k0 < width; k0 += SL_B) {
-            double a[SL_B];
-            int64_t c[SL_B];
-#pragma unroll
-            for (int u = 0; u < SL_B; ++u) {
-                const int64_t e = beg + (int64_t)min(k0 + u, width - 1) * 64 + lane;
-                a[u] = sv[e];
-                c[u] = ic + ldg[sd[e]];
-            }
-            double dc[SL_B];
-#pragma unroll
-            for (int u = 0; u < SL_B; ++u)
-                dc[u] = diag[min(max(c[u], (int64_t)0), (int64_t)n - 1)];
-#pragma unroll
-            for (int u = 0; u < SL_B; ++u) {
-                if (k0 + u >= len)
-                    continue;
-                if (c[u] != ic)
-                    off += fabs(a[u]);
-                const int s = slot_at(rpos, ic, c[u], nx, ny);
-                if (s >= 0) {
-                    myh[s] = bf16_of((float)(a[u] / d));
-                    myh[NBR + s] = bf16_of((float)(dc[u] / d));
-                }
-            }
-        }
-        if (live) {
-            const double margin = (d - off) / d;
-            if (!(d != 0.0) || !isfinite(margin))
-                *bad = 1u;
-            myh[27] = bf16_of((float)margin);
-        }
+    for (int64_t sl = (int64_t)blockIdx.x * 4 + wv; sl < A.nslice; sl += (int64_t)gridDim.x * 4) {
+        const uint32_t has = slice_features(A, sl, ldg, diag, lf[wv] + lane * FS_LD, bad);
+        if (slots && sl * 64 + lane < A.n)
+            slots[sl * 64 + lane] = has;
         wave_sync();
         for (int q = 0; q < 32; ++q) {
             const int r = 2 * q + (lane >> 5);
             const int64_t row = sl * 64 + r;
-            if (row < n)
+            if (row < A.n)
                 ((uint32_t *)(feat + row * NF))[lane & 31] = lf[wv][r * FS_LD + (lane & 31)];
         }
         wave_sync();
@@ -371,13 +441,67 @@ __device__ __forceinline__ s16x4 lds4(const uint16_t *p)
     return r;
 }
 
+// Four bf16 values, round to nearest even, by the hardware's paired conversion
+// (the same bits as bf16_of for every float that is not NaN, in 2 instructions
+// for about 16; the layers are bound by their VALU work beside the products).
+__device__ __forceinline__ s16x4 bf16x4_of(f32x4 v)
+{
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(s16x4, __builtin_convertvector(v, bf16x4));
+}
+
 __device__ __forceinline__ s16x4 relu_bf16(f32x4 c)
 {
-    s16x4 r;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-        r[q] = (short)bf16_of(fmaxf(c[q], 0.0f));
-    return r;
+        c[q] = fmaxf(c[q], 0.0f);
+    return bf16x4_of(c);
+}
+
+// The three layers on a 16-row tile: fb holds the tile's features in the B
+// layout (lane's row lane % 16, four features per step); h1, h2 and the
+// outputs o come in the result layout (lane l: outputs 4 (l / 16) + q of each
+// 16, row l % 16).
+__device__ __forceinline__ void layers(const WeightsLds &L, const s16x4 (&fb)[NF / 16],
+                                       s16x4 (&h1)[4], s16x4 (&h2)[4], f32x4 (&o)[2])
+{
+    const int lane = threadIdx.x & 63, col = lane & 15, kq = (lane >> 4) * 4;
+    // layer 1: H1^T (64 x 16) = W1^T (64 x 64) F^T (64 x 16)
+#pragma unroll
+    for (int ot = 0; ot < 4; ++ot) {
+        f32x4 c;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            c[q] = L.b1[ot * 16 + kq + q];
+#pragma unroll
+        for (int ks = 0; ks < NF / 16; ++ks)
+            c = mfma(lds4(&L.w1t[(ot * 16 + col) * NF + ks * 16 + kq]), fb[ks], c);
+        h1[ot] = relu_bf16(c);
+    }
+    // layer 2: H2^T (64 x 16) = W2^T (64 x 64) H1^T
+#pragma unroll
+    for (int ot = 0; ot < 4; ++ot) {
+        f32x4 c;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            c[q] = L.b2[ot * 16 + kq + q];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+            c = mfma(lds4(&L.w2t[(ot * 16 + col) * NH + ks * 16 + kq]), h1[ks], c);
+        h2[ot] = relu_bf16(c);
+    }
+    // layer 3: O^T (32 x 16) = W3^T (32 x 64) H2^T
+#pragma unroll
+    for (int ot = 0; ot < 2; ++ot) {
+        f32x4 c;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            c[q] = L.b3[ot * 16 + kq + q];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+            c = mfma(lds4(&L.w3t[(ot * 16 + col) * NH + ks * 16 + kq]), h2[ks], c);
+        o[ot] = c;
+    }
 }
 
 // Forward pass of 16-row tiles: O (n x 32 fp32); optionally the bf16 hidden
@@ -397,67 +521,22 @@ __global__ __launch_bounds__(256) void k_forward(int n, const uint16_t *__restri
          tile += (int64_t)gridDim.x * nw) {
         const int64_t row = tile * 16 + col;              // this lane's row in the B layout
         const bool live = row < n;
-        // layer 1: H1^T (64 x 16) = W1^T (64 x 64) F^T (64 x 16)
-        s16x4 fb[NF / 16];
+        s16x4 fb[NF / 16], h1[4], h2[4];
+        f32x4 o[2];
 #pragma unroll
-        for (int ks = 0; ks < NF / 16; ++ks) {
-            if (live) {
-                const uint2 v = *(const uint2 *)(feat + row * NF + ks * 16 + kq);
-                fb[ks][0] = (short)(v.x & 0xFFFF);
-                fb[ks][1] = (short)(v.x >> 16);
-                fb[ks][2] = (short)(v.y & 0xFFFF);
-                fb[ks][3] = (short)(v.y >> 16);
-            } else {
-                fb[ks] = s16x4{0, 0, 0, 0};
-            }
-        }
-        s16x4 h1[4];
+        for (int ks = 0; ks < NF / 16; ++ks)
+            fb[ks] = live ? lds4(feat + row * NF + ks * 16 + kq) : s16x4{0, 0, 0, 0};
+        layers(L, fb, h1, h2, o);
+        if (!live)
+            continue;
 #pragma unroll
-        for (int ot = 0; ot < 4; ++ot) {
-            f32x4 c;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                c[q] = L.b1[ot * 16 + kq + q];
-#pragma unroll
-            for (int ks = 0; ks < NF / 16; ++ks)
-                c = mfma(lds4(&L.w1t[(ot * 16 + col) * NF + ks * 16 + kq]), fb[ks], c);
-            h1[ot] = relu_bf16(c);
-        }
-        // layer 2: H2^T (64 x 16) = W2^T (64 x 64) H1^T
-        s16x4 h2[4];
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) {
-            f32x4 c;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                c[q] = L.b2[ot * 16 + kq + q];
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-                c = mfma(lds4(&L.w2t[(ot * 16 + col) * NH + ks * 16 + kq]), h1[ks], c);
-            h2[ot] = relu_bf16(c);
-        }
-        // layer 3: O^T (32 x 16) = W3^T (32 x 64) H2^T
-#pragma unroll
-        for (int ot = 0; ot < 2; ++ot) {
-            f32x4 c;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                c[q] = L.b3[ot * 16 + kq + q];
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-                c = mfma(lds4(&L.w3t[(ot * 16 + col) * NH + ks * 16 + kq]), h2[ks], c);
-            if (live)
-                *(f32x4 *)(O + row * NO + ot * 16 + kq) = c;
-        }
-        if (live && H1) {
+        for (int ot = 0; ot < 2; ++ot)
+            *(f32x4 *)(O + row * NO + ot * 16 + kq) = o[ot];
+        if (H1) {
 #pragma unroll
             for (int ot = 0; ot < 4; ++ot) {
-                uint2 a = {(uint32_t)(uint16_t)h1[ot][0] | ((uint32_t)(uint16_t)h1[ot][1] << 16),
-                           (uint32_t)(uint16_t)h1[ot][2] | ((uint32_t)(uint16_t)h1[ot][3] << 16)};
-                uint2 b = {(uint32_t)(uint16_t)h2[ot][0] | ((uint32_t)(uint16_t)h2[ot][1] << 16),
-                           (uint32_t)(uint16_t)h2[ot][2] | ((uint32_t)(uint16_t)h2[ot][3] << 16)};
-                *(uint2 *)(H1 + row * NH + ot * 16 + kq) = a;
-                *(uint2 *)(H2 + row * NH + ot * 16 + kq) = b;
+                *(uint2 *)(H1 + row * NH + ot * 16 + kq) = __builtin_bit_cast(uint2, h1[ot]);
+                *(uint2 *)(H2 + row * NH + ot * 16 + kq) = __builtin_bit_cast(uint2, h2[ot]);
             }
         }
     }
@@ -492,14 +571,11 @@ __global__ __launch_bounds__(256) void k_assemble(int n, const int32_t *__restri
     }
 }
 
-// float16 code of an fp32 value: one rounding to nearest even; magnitudes
-// from 65520 up become infinity, NaN the quiet NaN.
+// float16 code of an fp32 value: one rounding to nearest even (the hardware
+// conversion: magnitudes from 65520 up become infinity); NaN the quiet NaN.
 __device__ __forceinline__ uint16_t f16_code(float f)
 {
-    const double v = (double)f;
-    if (!(fabs(v) < 65520.0))
-        return (uint16_t)(v != v ? 0x7E00u : (0x7C00u | (sign_of(v) << 15)));
-    return (uint16_t)(rne_code<10, -14, 15>(v) | (sign_of(v) << 15));
+    return f != f ? (uint16_t)0x7E00u : __builtin_bit_cast(uint16_t, (_Float16)f);
 }
 
 // The stored form's codes: on the slots present in A's row the float16 code
@@ -547,57 +623,59 @@ __global__ __launch_bounds__(256) void k_stencil_pack(int n, int64_t ld,
     }
 }
 
-// The stored form's codes from the sliced-ELL copy with diagonal indices
-// (the same codes): one wave per 64-row slice, lane = row, the row's slots
-// marked in an LDS block of the wave's own (slot-major, 64 rows), then each
-// slot's 64 codes written as one run.  Slices past the copy's (rows up to
-// ld) are written as 0.
-__global__ __launch_bounds__(256) void k_stencil_pack_sell(
-    int n, int64_t ld, int64_t nslice, const int32_t *__restrict__ rp,
-    const int64_t *__restrict__ sp, const uint8_t *__restrict__ sd,
-    const int32_t *__restrict__ sdiag, int ndiag, int nx, int ny, const float *__restrict__ O,
-    uint16_t *__restrict__ codes)
+// The stored form's codes (the same) from the features and the slots each row
+// stores: a wave takes 64 rows, runs the layers on their four tiles, puts the
+// float16 codes into LDS, slot-major, and writes each slot's run of 64.  The
+// outputs (128 bytes a row) stay in registers, and A is not walked again: at
+// 128^3 the forward pass and the packing from A took 186 + 210 us as kernels
+// of their own, this one 200 us.  Forming the features here too, from LDS, was slower (461 us
+// for all three against 242 + 128 + 215): the weights leave two waves per
+// SIMD, too few for the chain of loads behind a feature.
+__global__ __launch_bounds__(256) void k_forward_codes(int n, int64_t ld,
+                                                       const uint16_t *__restrict__ feat,
+                                                       const uint32_t *__restrict__ slots,
+                                                       const uint16_t *__restrict__ wq,
+                                                       const float *__restrict__ prm,
+                                                       uint16_t *__restrict__ codes)
 {
-    __shared__ int32_t ldg[CBG_SELL_MAX_DIAG];
-    __shared__ uint16_t lc[4][NSLOT * 64];
-    for (int t = threadIdx.x; t < ndiag; t += blockDim.x)
-        ldg[t] = sdiag[t];
-    __syncthreads();
+    __shared__ WeightsLds L;
+    __shared__ uint32_t lcw[4][NSLOT * 32];
+    stage_weights(L, wq, prm);
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    uint16_t *mine = lc[wv];
-    const int64_t nsl_ld = ld / 64;                      // ld is a multiple of 256
-    for (int64_t sl = (int64_t)blockIdx.x * 4 + wv; sl < nsl_ld; sl += (int64_t)gridDim.x * 4) {
-        for (int s = 0; s < NSLOT; ++s)
-            mine[s * 64 + lane] = 0;
-        wave_sync();
-        if (sl < nslice) {
-            const int64_t i = sl * 64 + lane;
-            const bool live = i < n;
-            const int64_t ic = live ? i : (int64_t)n - 1;
-            const int64_t beg = sp[sl];
-            const int width = (int)((sp[sl + 1] - beg) / 64);
-            const int len = live ? rp[i + 1] - rp[i] : 0;
-            const RowPos rpos = row_pos(ic, nx, ny);
-            for (int k0 = 0; k0 < width; k0 += SL_B) {
-                int sl_of[SL_B];
-                float o[SL_B];
+    const int col = lane & 15, kq = (lane >> 4) * 4;
+    uint16_t *lc = (uint16_t *)lcw[wv];
+    const int64_t runs = ld / 64, step = (int64_t)gridDim.x * 4;     // ld is a multiple of 256
+    for (int64_t run = (int64_t)blockIdx.x * 4 + wv; run < runs; run += step) {
+        // the four tiles' features and slots in flight together (rows >= n
+        // store no slot)
+        s16x4 fb[4][NF / 16];
+        uint32_t has[4];
 #pragma unroll
-                for (int u = 0; u < SL_B; ++u) {
-                    const int64_t e = beg + (int64_t)min(k0 + u, width - 1) * 64 + lane;
-                    sl_of[u] = slot_at(rpos, ic, ic + ldg[sd[e]], nx, ny);
+        for (int t = 0; t < 4; ++t) {
+            const int64_t row = run * 64 + t * 16 + col, rc = min(row, (int64_t)n - 1);
+#pragma unroll
+            for (int ks = 0; ks < NF / 16; ++ks)
+                fb[t][ks] = lds4(feat + rc * NF + ks * 16 + kq);
+            has[t] = row < n ? slots[rc] : 0u;
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            s16x4 h1[4], h2[4];
+            f32x4 o[2];
+            layers(L, fb[t], h1, h2, o);
+#pragma unroll
+            for (int ot = 0; ot < 2; ++ot)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int p = ot * 16 + kq + q;
+                    if (p < NSLOT)
+                        lc[p * 64 + t * 16 + col] =
+                            (has[t] >> p) & 1u ? f16_code(o[ot][q]) : (uint16_t)0;
                 }
-#pragma unroll
-                for (int u = 0; u < SL_B; ++u)
-                    o[u] = O[ic * NO + max(sl_of[u], 0)];
-#pragma unroll
-                for (int u = 0; u < SL_B; ++u)
-                    if (k0 + u < len && sl_of[u] >= 0)
-                        mine[sl_of[u] * 64 + lane] = f16_code(o[u]);
-            }
         }
         wave_sync();
-        for (int s = 0; s < NSLOT; ++s)
-            codes[(int64_t)s * ld + sl * 64 + lane] = mine[s * 64 + lane];
+        for (int e = lane; e < NSLOT * 32; e += 64)
+            *(uint32_t *)(codes + (int64_t)(e >> 5) * ld + run * 64 + 2 * (e & 31)) = lcw[wv][e];
         wave_sync();
     }
 }
@@ -975,7 +1053,7 @@ __global__ void k_loss_fold(const double *__restrict__ part, int nb, double scal
 // one contiguous 128-byte read, and nothing goes through LDS but the weights.
 // Latency-bound with one wave per SIMD (160 accumulators a lane), so the next
 // tile's loads run under the current tile's 72 products: 386 us at 262,144
-// rows with the tile staged in LDS value by value, 65 us now (the fold of the
+// rows with the tile staged in LDS value by value, 101 us now (the fold of the
 // blocks' partials took 124 us with 512 of them in turn per parameter).
 // ---------------------------------------------------------------------------
 
@@ -1007,16 +1085,24 @@ __device__ __forceinline__ void by_column(const uint2 (&x)[4], s16x4 (&op)[4])
 // bf16 of the gradient where the activation is positive, else 0
 __device__ __forceinline__ s16x4 masked_bf16(f32x4 c, s16x4 act)
 {
-    s16x4 r;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-        r[q] = (short)bf16_of(f_of((uint16_t)act[q]) > 0.0f ? c[q] : 0.0f);
-    return r;
+        c[q] = f_of((uint16_t)act[q]) > 0.0f ? c[q] : 0.0f;
+    return bf16x4_of(c);
 }
-__device__ __forceinline__ float sum4(s16x4 v)
+// a column's running sum over the tile's 16 rows in turn, four of them on each
+// of its lanes c, c + 16, c + 32, c + 48 (all get the sum)
+__device__ __forceinline__ float add_column(float sum, s16x4 v, int c)
 {
-    return (f_of((uint16_t)v[0]) + f_of((uint16_t)v[1])) +
-           (f_of((uint16_t)v[2]) + f_of((uint16_t)v[3]));
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        float s = sum;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            s += f_of((uint16_t)v[q]);
+        sum = __shfl(s, c + 16 * h);
+    }
+    return sum;
 }
 
 // one tile's inputs as a lane loads them
@@ -1126,25 +1212,13 @@ __global__ __launch_bounds__(256) void k_backward(int n, const uint16_t *__restr
                 gw2[a][b] = mfma(h1c[a], d2[b], gw2[a][b]);
                 gw1[a][b] = mfma(fc[a], d1[b], gw1[a][b]);
             }
-            gb2[a] += sum4(d2[a]);
-            gb1[a] += sum4(d1[a]);
+            gb2[a] = add_column(gb2[a], d2[a], c);
+            gb1[a] = add_column(gb1[a], d1[a], c);
         }
-        gb3[0] += sum4(oc[0]);
-        gb3[1] += sum4(oc[1]);
+        gb3[0] = add_column(gb3[0], oc[0], c);
+        gb3[1] = add_column(gb3[1], oc[1], c);
         cur = nxt;
     }
-    // the four row groups of a column
-    auto groups = [](float v) {
-        v += __shfl_xor(v, 16);
-        return v + __shfl_xor(v, 32);
-    };
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        gb1[a] = groups(gb1[a]);
-        gb2[a] = groups(gb2[a]);
-    }
-    gb3[0] = groups(gb3[0]);
-    gb3[1] = groups(gb3[1]);
     // the block's sums in parameter order, the waves in turn; every parameter
     // is held by exactly one lane of a wave (the biases by g = 0)
     __syncthreads();                            // the weights are done with
@@ -1313,7 +1387,7 @@ namespace {
 
 constexpr size_t SALIGN = 256;
 constexpr int MAXB_ROW = 4096;     // grid cap of the row-parallel kernels
-constexpr int MAXB_BACK = 256;     // grid cap of the backward pass: a block per CU (partials)
+constexpr int MAXB_BACK = 512;     // grid cap of the backward pass (partials)
 
 size_t salign(size_t x) { return (x + SALIGN - 1) / SALIGN * SALIGN; }
 
@@ -1403,15 +1477,19 @@ void enqueue_diag(const cbg_csr *A, double *diag, hipStream_t s)
     }
 }
 
+SellDix sell_dix(const cbg_csr *A, const int32_t grid[3])
+{
+    return {A->n,        A->sell_ndiag, grid[0],     grid[1],     ((int64_t)A->n + 63) / 64,
+            A->row_ptr,  A->sell_ptr,   A->sell_dix, A->sell_val, A->sell_diag};
+}
+
 // The features, from the sliced-ELL copy when A carries one
 void enqueue_features(const cbg_csr *A, const int32_t grid[3], const double *diag, uint16_t *feat,
-                      unsigned *bad, hipStream_t s)
+                      unsigned *bad, hipStream_t s, uint32_t *slots = nullptr)
 {
     if (sell_dix_of(A)) {
-        hipLaunchKernelGGL(k_features_sell, dim3(slice_grid(A->n)), dim3(256), 0, s, A->n,
-                           (int64_t)(A->n + 63) / 64, A->row_ptr, A->sell_ptr, A->sell_dix,
-                           A->sell_val, A->sell_diag, A->sell_ndiag, grid[0], grid[1], diag,
-                           feat, bad);
+        hipLaunchKernelGGL(k_features_sell, dim3(slice_grid(A->n)), dim3(256), 0, s,
+                           sell_dix(A, grid), diag, feat, slots, bad);
     } else {
         hipLaunchKernelGGL(k_features, dim3(group_grid(A->n)), dim3(256), 0, s, A->n,
                            A->row_ptr, A->col_idx, A->val, grid[0], grid[1], diag, feat, bad);
@@ -1454,7 +1532,7 @@ void enqueue_forward(int64_t n, const uint16_t *feat, const uint16_t *w, const f
                      uint16_t *h1, uint16_t *h2, hipStream_t s)
 {
     // two blocks per CU: what its registers allow; more only stage the
-    // weights again (262,144 rows in 2048 blocks: 99 us, 512: 53 us)
+    // weights again (262,144 rows in 2048 blocks: 99 us, 512: 54 us)
     hipLaunchKernelGGL(k_forward, dim3(tile_grid(n, 512)), dim3(256), 0, s, (int)n, feat, w, prm,
                        O, h1, h2);
 }
@@ -1620,14 +1698,15 @@ int cbg_learned_build_stencil(const cbg_csr *A, const int32_t grid[3], const uin
     const int64_t ld = cbg_basis_ld(A->n);
     SP_TRY(hipMemsetAsync(W.bad, 0, sizeof(unsigned), s));
     enqueue_diag(A, W.diag, s);
-    enqueue_features(A, grid, (const double *)W.diag, W.feat, W.bad, s);
-    enqueue_forward(A->n, W.feat, weights, params, W.O, nullptr, nullptr, s);
     if (sell_dix_of(A)) {
-        hipLaunchKernelGGL(k_stencil_pack_sell, dim3(slice_grid(ld)), dim3(256), 0, s, A->n, ld,
-                           (int64_t)(A->n + 63) / 64, A->row_ptr, A->sell_ptr, A->sell_dix,
-                           A->sell_diag, A->sell_ndiag, grid[0], grid[1], (const float *)W.O,
-                           p_stencil);
+        uint32_t *slots = (uint32_t *)W.O;          // a word a row where 32 outputs would be
+        enqueue_features(A, grid, (const double *)W.diag, W.feat, W.bad, s, slots);
+        const int gb = (int)std::min<int64_t>(ld / 256, 512);       // two blocks per CU
+        hipLaunchKernelGGL(k_forward_codes, dim3(gb), dim3(256), 0, s, A->n, ld, W.feat, slots,
+                           weights, params, p_stencil);
     } else {
+        enqueue_features(A, grid, (const double *)W.diag, W.feat, W.bad, s);
+        enqueue_forward(A->n, W.feat, weights, params, W.O, nullptr, nullptr, s);
         const int gp = (int)std::min<int64_t>((ld + PK_ROWS - 1) / PK_ROWS, MAXB_ROW);
         hipLaunchKernelGGL(k_stencil_pack, dim3(std::max(gp, 1)), dim3(256), 0, s, A->n, ld,
                            A->row_ptr, A->col_idx, grid[0], grid[1], (const float *)W.O,
