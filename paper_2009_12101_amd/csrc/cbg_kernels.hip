@@ -476,10 +476,13 @@ __global__ __launch_bounds__(BLK) void k_spmv(int n, int64_t ldy, const int32_t 
         ep = param_from_scale(fmt, *qscale);
     }
     constexpr int TPR = BLK / RPB;          // threads per row in the sum phase
-    // products per thread per batch: eight on the short-row shape (one batch
-    // covers the block's 256 rows of a 7-point matrix: 36.1 against 38.1 us
-    // at 128^3), four on the long-row shapes (27-point rows: 165 against 167)
-    constexpr int UNR = RPB >= 256 ? 8 : 4;
+    // Products per thread per batch.  The kernel waits on the chain of index,
+    // gather and barrier, so a batch is as large as the block's rows at the
+    // mean length fill it: eight for 256 rows of a 7-point matrix (36.1
+    // against 38.1 us with four at 128^3), seven for 64 27-point rows (6.75
+    // per thread, 154 against 159 us; eight loads more than it uses, 162).
+    // Beyond that registers cost waves: sixteen took 238 us.
+    constexpr int UNR = RPB >= 256 ? 8 : CAP == 3072 ? 7 : 4;
     __shared__ double prod[CAP];
     __shared__ int lrp[RPB + 1];
     const int tid = threadIdx.x;
@@ -3039,14 +3042,17 @@ static int grid_for(int64_t work_items, int per_block)
 
 // Launch shape of the CSR-stream SpMV from the mean row length: rows per
 // block and the LDS product buffer (entries), sized so a block's products
-// fit it at up to about 8, 32 and 64 entries per row.  A smaller buffer
-// lets more blocks share a CU: on the 27-point stencil (26.6 per row) 64
-// rows with 2048 entries run 15% faster than 128 rows with 4096.
+// fit it at up to about 8, 48 and 64 entries per row.  64 rows of up to 30
+// entries on average take 3072: 64 uneven rows often hold more than the
+// 2048 that 27-point rows need, and such a block sums its rows one gather
+// at a time.  1,000,003 rows of 4 to 82 entries (26 on average): 128 us
+// against 135 with 2048; 27-point rows at 128^3 do not change (154, 153).
+// 4096 lets fewer blocks share a CU: 124 and 173.
 int spmv_shape_of(int n, int64_t nnz)
 {
     double avg = n > 0 ? (double)nnz / n : 1.0;
     if (avg <= 7.5) return SPMV_R256_C2K;
-    if (avg <= 30.0) return SPMV_R64_C2K;
+    if (avg <= 30.0) return SPMV_R64_C3K;
     if (avg <= 60.0) return SPMV_R64_C4K;
     return SPMV_R32_C4K;
 }
@@ -3223,7 +3229,7 @@ int launch_spmv(const SpmvArgs &a, hipStream_t s)
         return spmv_sell(a, s);
     switch (a.sg) {
     case SPMV_R256_C2K: return spmv_shape<256, 2048>(a, s);
-    case SPMV_R64_C2K: return spmv_shape<64, 2048>(a, s);
+    case SPMV_R64_C3K: return spmv_shape<64, 3072>(a, s);
     case SPMV_R64_C4K: return spmv_shape<64, 4096>(a, s);
     case SPMV_RP64_C2K: return spmv_rp_shape<64, 2048>(a, s);
     default: return spmv_shape<32, 4096>(a, s);

@@ -78,7 +78,7 @@ enum { RR_NB = 0, RR_SCALE = 1, RR_NORM2 = 2, RR_RESID = 3, RR_H = 4, RR_U = 5, 
        RR_C2 = 14 }; // close of the one-pass update (rows 0 and 1; a hard step's rows j+2, j+3)
 
 // SpMV launch shapes: rows per block and LDS product-buffer entries
-enum { SPMV_R256_C2K = 0, SPMV_R64_C2K = 1, SPMV_R64_C4K = 2, SPMV_R32_C4K = 3,
+enum { SPMV_R256_C2K = 0, SPMV_R64_C3K = 1, SPMV_R64_C4K = 2, SPMV_R32_C4K = 3,
        SPMV_RP64_C2K = 4 };   // row-parallel gather (k_spmv_rp)
 int spmv_shape_of(int n, int64_t nnz);     // from the mean row length
 int spmv_rows(int shape);

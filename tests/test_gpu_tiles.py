@@ -82,3 +82,28 @@ def test_back_substitution_sizes(orc, dev, m):
     r = cbg.solve(cbg.DeviceCSR.from_host(A, dev), torch.from_numpy(b).to(dev), **kw)
     assert r.iterations == o["iterations"]
     assert np.linalg.norm(r.x.cpu().numpy() - o["x"]) <= 1e-8 * np.linalg.norm(o["x"])
+
+
+@pytest.mark.parametrize("first", [1791, 1792, 1793, 2048, 2049, 3071, 3072, 3073, 5000])
+def test_spmv_product_buffer_edges(orc, dev, first):
+    """CSR SpMV of 64-row blocks around one batch per thread (7 x 256) and
+    the product buffer (3072): the first block holds `first` entries, the
+    others 20 a row.  |err| <= (entries + 1) * 2^-53 * sum |a x| per row."""
+    import scipy.sparse as sp
+    from paper_2009_12101_amd.problems import CSR
+    import paper_2009_12101_amd as cbg
+    n = 64 * 40 + 17
+    rng = np.random.default_rng(first)
+    per = np.full(n, 20)
+    per[:64] = first // 64
+    per[:first % 64] += 1
+    rp = np.concatenate([[0], np.cumsum(per)]).astype(np.int32)
+    ci = np.concatenate([np.sort(rng.choice(n, k, replace=False)) for k in per]).astype(np.int32)
+    A = sp.csr_matrix((rng.standard_normal(rp[-1]), ci, rp), shape=(n, n))
+    x = rng.standard_normal(n)
+    Ad = cbg.DeviceCSR.from_host(CSR(n, rp, ci, A.data), dev, sell=False)
+    y = cbg.spmv(Ad, torch.from_numpy(x).to(dev)).cpu().numpy()
+    bound = (per + 1) * 2.0 ** -53 * (abs(A) @ abs(x))
+    ref = np.array([np.sum((A.data[a:b] * x[A.indices[a:b]]).astype(np.longdouble))
+                    for a, b in zip(rp[:-1], rp[1:])], dtype=np.float64)
+    assert np.all(np.abs(y - ref) <= bound)
