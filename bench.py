@@ -211,7 +211,7 @@ def trace_summary(trace_csv: str, cfg: Config) -> dict:
     kernels = {
         step_spmv: lambda j: sp_bytes,
         f"k_multidot<{fid}, true>": lambda j: j * n * bs + 8.0 * n + n * bs,
-        f"k_update<{fid}, 6>": lambda j: j * n * bs + 16.0 * n,
+        f"k_update<{fid}, 6,": lambda j: j * n * bs + 16.0 * n,
         # the stored form of the learned preconditioner with steps 13-14:
         # 27 codes of 2 bytes, w, dinv and z of 8 bytes, the stored entry
         f"k_stencil<{fid}, 0": lambda j: 54.0 * n + 24.0 * n + n * bs,

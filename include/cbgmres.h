@@ -278,7 +278,8 @@ size_t cbg_workspace_bytes(int32_t n, int32_t restart, int32_t format, int32_t p
  * whenever the recurrence residual signals convergence (Section 6.2: the
  * solve continues from the explicit residual if it misses tol).
  * If ||b|| = 0 the solution is x = 0.  The host synchronises with the
- * stream once per restart cycle. */
+ * stream once per restart cycle, and once more in the cycle that meets the
+ * solve's first near-breakdown step (see steps 5-10 below). */
 int cbgmres_solve(const cbg_csr *A, const double *b, double *x, const cbg_opts *opt,
                   void *workspace, size_t ws_bytes, void *stream, cbg_result *res,
                   double *hist, int64_t hist_len);

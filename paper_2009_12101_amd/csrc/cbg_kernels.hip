@@ -1,21 +1,25 @@
 // gfx950 kernels of the CB-GMRES hot path and their host launchers.
 //
-// One Arnoldi step of Fig. 1 (Section 3) runs as
-//   spmv       w = A M^-1 v; block partials of ||w||^2           (steps 3-4)
-//   multidot   block partials of h = V_j^T w                     (step 5)
-//   reduce     h, omega = ||A M^-1 v||
-//   update     w -= V_j h                                        (step 5)
-//   multidot   block partials of u = V_j^T w, ||w||^2, max|w_i|  (steps 6, 8)
-//   reduce     u, h_{j+1,j} = ||w||; re-orthogonalise iff
-//              h_{j+1,j} < eta * omega (step 7), else finish the step
-//   update     w -= V_j u, partials of ||w||^2, max|w_i|         (steps 8-10)
-//   reduce     h += u, h_{j+1,j}; breakdown test; Givens         (steps 11-12, 16-17)
-//   normalize  v = w / h_{j+1,j}; V_{j+1} = enc(v)               (steps 13-14)
-// The re-dot u = V_j^T w is computed with the norm of w in the same pass;
-// it is used only when step 7 asks for it.  Producers write block partials
-// with plain stores and a one-block reduce kernel folds them in fixed order,
-// so sums are bitwise reproducible and no block fences against another.
-// The host only enqueues kernels; it synchronises once per restart cycle.
+// One Arnoldi step of Fig. 1 (Section 3) runs by default as
+//   spmv       v = w / t stored as enc(v), w = A M^-1 v, block partials of
+//              ||w||^2 (steps 13-14 of the step before, 3-4); long rows and
+//              most preconditioners have a pass of their own before it
+//   multidot   block partials of h = V_j^T w and of the newest Gram row
+//              (steps 5, 8)
+//   reduce     h, the Gram row, omega = ||A M^-1 v||
+//   update     u = h - G h, the step-7 decision, w -= V_j (h + u) or
+//              V_j h, its norms (steps 5-10); one more block applies the
+//              stored rotations; the block that finishes last folds the
+//              norms, tests for breakdown and forms the new rotation
+//              (steps 11-12, 16-17)
+// Steps of few tiles leave the reduce to the update too (RU_SMALL).  A step
+// whose norm cannot come from Pythagoras (a hard step) gets an explicit
+// second pass: the first one pauses the cycle for the host to enqueue it,
+// from then on every step carries it (U_HARD, nothing on other steps).  Producers write block partials
+// with plain stores; a kernel launched later, or the block that finishes
+// last, folds them in fixed order, so sums are bitwise reproducible.
+// The host only enqueues kernels; it synchronises once per restart cycle,
+// and once more in the cycle that meets a solve's first hard step.
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -1432,9 +1436,10 @@ enum { U_PLAIN = 0, U_STEP1 = 1, U_STEP2 = 2, U_SOLUTION = 3, U_COMBINE = 4, U_S
 // t / omega stays above 0.3, so the explicit form is a safeguard for
 // near-breakdowns (clustered spectra), not the common path.
 constexpr double HARD_RATIO = 1e-4;
-// Tile blocks of the second-pass kernel (U_HARD).  It is launched on every
-// step and returns at once unless the step is hard, so a small grid keeps
-// that launch cheap; a hard step's second pass streams the basis with it.
+// Tile blocks of the second-pass kernel (U_HARD).  After a solve's first hard
+// step it is launched on every step and returns at once unless the step is
+// hard, so a small grid keeps that launch cheap; a hard step's second pass
+// streams the basis with it.
 constexpr int HARD_BLOCKS = 256;
 
 // The one-pass update's G h for one wave: out[k] = sum over l in [l0, l1) of
