@@ -1745,11 +1745,13 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
         // updates with h only and adds the explicit re-dot of the result.
         const size_t ldg = (size_t)st->m + 1;
         if constexpr (SMALL) {
-            // the SpMV's partials are at most one per lane here: in flight
-            // with the multi-dot's
+            // The SpMV's partials, a quarter per wave and a lane's in turn, as in
+            // the fold that this replaces.  Up to 256 of them are one per lane,
+            // in flight with the multi-dot's; the CSR kernels leave one per 64
+            // rows, or per 32 long ones: up to 512 or 1024 on a small step.
             const int q4 = (nb_spmv + RWAVES - 1) / RWAVES;
             const int lo = min(wv * q4, nb_spmv), cnt = min(q4, nb_spmv - lo);
-            const double om = lane < cnt ? spmv_part[lo + lane] : 0.0;
+            double om = lane < cnt ? spmv_part[lo + lane] : 0.0;
             for (int e = tid; e < 2 * j; e += BLK) {
                 const int k = e < j ? e : e - j;
                 const double a =
@@ -1766,7 +1768,10 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
                     }
                 }
             }
-            const double oq = wave_sum(0.0 + om);
+            om = 0.0 + om;
+            for (int i = lane + 64; i < cnt; i += 64)
+                om += spmv_part[lo + i];
+            const double oq = wave_sum(om);
             if (lane == 0)
                 lr[0][wv] = oq;
             __syncthreads();
