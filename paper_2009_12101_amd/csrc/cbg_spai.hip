@@ -15,6 +15,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "../../include/cbgmres.h"
 #include "cbg_device.hpp"
@@ -829,6 +830,21 @@ __device__ __forceinline__ void quad_transpose(double *d, int q)
         }
 }
 
+// A row's entries in batches of four, one per lane of the quad: f(p0, whole)
+// with whole true_type for a full batch.  In the last, partial one only the
+// entries that are there count: a lane past the row's end takes part in the
+// moves between lanes with row i's index, and 0 times an infinity there would
+// be a NaN.  (The grid's rows of 27 have six full batches, which need no test.)
+template <typename Fn>
+__device__ __forceinline__ void quad_batches(int beg, int end, Fn f)
+{
+    int p0 = beg;
+    for (; p0 + 4 <= end; p0 += 4)
+        f(p0, std::true_type{});
+    if (p0 < end)
+        f(p0, std::false_type{});
+}
+
 // Y = P V.  FROM_O: P_ic = fl32((delta + O[slot]) / a_ii) from the network's
 // output and the diagonal (the values k_assemble writes), else P's values.
 template <bool K32, bool FROM_O>
@@ -850,9 +866,9 @@ __global__ __launch_bounds__(256) void k_quad_pv(int n, int K, const int32_t *__
 #pragma unroll
         for (int e = 0; e < 8; ++e)
             acc[e] = 0.0;
-        for (int p0 = beg; p0 < end; p0 += 4) {
+        quad_batches(beg, end, [&](int p0, auto whole) __attribute__((always_inline)) {
             const int p = p0 + q;
-            const bool in = p < end;
+            const bool in = whole || p < end;
             const int c = in ? ci[p] : (int)i;
             float a = 0.0f;
             if constexpr (FROM_O) {
@@ -869,11 +885,12 @@ __global__ __launch_bounds__(256) void k_quad_pv(int n, int K, const int32_t *__
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const double at = (double)quad_lane(a, t);
+                if (whole || p0 + t < end)
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    acc[e] = fma(at, v[t][e], acc[e]);
+                    for (int e = 0; e < 8; ++e)
+                        acc[e] = fma(at, v[t][e], acc[e]);
             }
-        }
+        });
         if constexpr (K32) {
 #pragma unroll
             for (int e = 0; e < 8; e += 2) {
@@ -899,9 +916,9 @@ __device__ __forceinline__ void quad_row(const int32_t *__restrict__ ci,
 #pragma unroll
     for (int e = 0; e < 8; ++e)
         acc[e] = 0.0;
-    for (int p0 = beg; p0 < end; p0 += 4) {
+    quad_batches(beg, end, [&](int p0, auto whole) __attribute__((always_inline)) {
         const int p = p0 + q;
-        const bool in = p < end;
+        const bool in = whole || p < end;
         const int c = in ? ci[p] : (int)i;
         const double a = in ? val[p] : 0.0;
         double x[4][8];
@@ -911,11 +928,12 @@ __device__ __forceinline__ void quad_row(const int32_t *__restrict__ ci,
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const double at = quad_lane(a, t);
+            if (whole || p0 + t < end)
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                acc[e] = fma(at, x[t][e], acc[e]);
+                for (int e = 0; e < 8; ++e)
+                    acc[e] = fma(at, x[t][e], acc[e]);
         }
-    }
+    });
 }
 
 // R = A Y - V, and block partials of ||R||_F^2.
