@@ -1167,7 +1167,9 @@ __global__ __launch_bounds__(256) void k_backward(int n, const uint16_t *__restr
         gb1[a] = gb2[a] = gb3[a & 1] = 0.0f;
     }
     const int64_t ntile = ((int64_t)n + 15) / 16, step = (int64_t)gridDim.x * nw;
-    // rows >= n read row n - 1 and a zero dO, which zeroes all they add
+    // rows >= n read row n - 1 and a zero dO; clear() makes the rest of them 0
+    // when the tile's turn comes (an infinite activation of row n - 1 times
+    // that dO would be a NaN)
     auto load = [&](int64_t tile, TileIn &x) {
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
@@ -1185,6 +1187,15 @@ __global__ __launch_bounds__(256) void k_backward(int n, const uint16_t *__restr
         for (int t = 0; t < 4; ++t)
             x.h2r[t] = *(const uint2 *)(H2 + rc * NH + 16 * t + 4 * g);
     };
+    auto clear = [&](int64_t tile, TileIn &x) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            if (tile * 16 + 4 * g + t >= n)
+                x.f[t] = x.h1[t] = x.h2[t] = uint2{0u, 0u};
+            if (tile * 16 + c >= n)
+                x.h2r[t] = uint2{0u, 0u};
+        }
+    };
     int64_t tile = (int64_t)blockIdx.x * nw + wave;
     TileIn cur;
     if (tile < ntile)
@@ -1193,6 +1204,8 @@ __global__ __launch_bounds__(256) void k_backward(int n, const uint16_t *__restr
         TileIn nxt;
         load(min(tile + step, ntile - 1), nxt);
         __builtin_amdgcn_sched_barrier(0);
+        if (tile * 16 + 16 > n)
+            clear(tile, cur);
         const s16x4 ob[2] = {as_s16x4(cur.dOr[0]), as_s16x4(cur.dOr[1])};
         s16x4 fc[4], h1c[4], h2c[4], oc[2];
         by_column(cur.f, fc);

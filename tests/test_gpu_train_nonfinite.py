@@ -2,14 +2,16 @@
 
 The sparse products take a row's entries four at a time: the lanes past the
 row's end belong to no entry and must not bring in row i of the vectors, which
-0 * inf would turn into a NaN.  Against the oracle's plain sums, entry by
-entry: the same infinities and NaNs, and the finite values within the bounds
-of the finite cases (1e-10 for dL/dP).
+0 * inf would turn into a NaN.  The backward pass takes 16 rows at a time: the
+rows past n repeat no activation.  Both against the oracle's plain sums, entry
+by entry: the same infinities and NaNs, and the finite values within the
+bounds of the finite cases (1e-10 for dL/dP, 1e-3 for the gradients through
+the bf16 roundings).
 """
 import numpy as np
 import pytest
 
-from tests.test_gpu_spai import S  # noqa: F401
+from tests.test_gpu_spai import S, bits_bf16, random_params, split_grad, to_device  # noqa: F401
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -62,3 +64,27 @@ def test_row_ends_bring_in_no_infinity(S, dev, reach, K):
                                 torch.from_numpy(pv.astype(np.float32)).to(dev), Vd, 1.0 / K)
     assert loss.item() == np.inf
     same(got.cpu().numpy(), dP, 1e-10)
+
+
+@pytest.mark.parametrize("n", [1, 17, 47])
+@pytest.mark.parametrize("where", ["F", "H1", "H2"])
+def test_rows_past_n_repeat_no_activation(S, dev, n, where):
+    """One column of the last row's features or activations is infinite, the
+    last tile is ragged, and every activation of that row is positive: the
+    column's gradients are infinite, not NaN, and the others stay finite."""
+    import paper_2009_12101_amd as cbg
+    print(f"backward {where} n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    prm = random_params(S, 9)
+    X = {"F": S.bf16(rng.standard_normal((n, 64))), "H1": S.bf16(0.1 + rng.random((n, 64))),
+         "H2": S.bf16(0.1 + rng.random((n, 64)))}
+    X[where][n - 1, 5] = np.inf
+    dO = S.bf16(rng.standard_normal((n, 32)) * 1e-2)
+    ref = S.backward(X["F"], X["H1"], X["H2"], prm["W2"], prm["W3"], dO)
+    assert sum(np.isinf(r).sum() for r in ref.values()) >= 32
+    assert not any(np.isnan(r).any() for r in ref.values())
+    _, weights = to_device(prm, dev)
+    args = [bits_bf16(t).to(dev) for t in (X["F"], X["H1"], X["H2"], dO)] + [weights]
+    got = split_grad(cbg.mlp_backward(*args).cpu().numpy())
+    for k in ref:
+        same(got[k], ref[k], 1e-3)
