@@ -617,9 +617,10 @@ int cbgmres_solve(const cbg_csr *A, const double *b, double *x, const cbg_opts *
                     }
                 }
                 if (prof_spmv) {
-                    // the step SpMV: the plain product when a pass formed M^-1 v,
-                    // else the gather variant, which also stores v_j
-                    const bool gather = !norm_pass && prev_pc != CBG_PC_STENCIL &&
+                    // the step SpMV as it was launched: the plain product when a
+                    // pass formed M^-1 v, else the gather variant, which also
+                    // stores v_j
+                    const bool gather = !pass && prev_pc != CBG_PC_STENCIL &&
                                         prev_pc != CBG_PC_SPARSE && prev_pc != CBG_PC_BLOCK_JACOBI;
                     for (int j = 1; j <= jl; ++j) {
                         if (!ev_on[j])
