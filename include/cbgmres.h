@@ -183,11 +183,11 @@ typedef struct {
  * entry by t (one division per nonzero instead of per row) and with Jacobi
  * reads D^-1 per nonzero.
  * Neither bit: the pass when the mean row length exceeds 12 nonzeros or the
- * preconditioner is Jacobi, the gather otherwise (up to 65536 rows the pass's
- * work runs in the gather too, which saves its launch; model_bytes counts
- * the pass).  Both bits: argument
- * error.  SPMV_VHAT and the block-Jacobi preconditioner always take their
- * own paths. */
+ * preconditioner is Jacobi, the gather otherwise (up to 65536 rows of a
+ * matrix whose sliced-ELL copy has at most 32 diagonals the pass's work runs
+ * in the gather too, which saves its launch; model_bytes counts the pass).
+ * Both bits: argument error.  SPMV_VHAT and the block-Jacobi preconditioner
+ * always take their own paths. */
 #define CBG_FLAG_NORMALISE_PASS 64
 #define CBG_FLAG_NORMALISE_GATHER 128
 /* Steps 5-10 (CGS with the conditional second pass).  By default:

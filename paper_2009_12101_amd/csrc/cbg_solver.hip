@@ -239,8 +239,16 @@ struct CycleEvents {
 // launches that find the cycle finished and return at once.
 constexpr int STEP_CHUNK = 16;
 
-// Rows up to which steps 13-14 always run inside the next SpMV's gather.
-constexpr int GATHER_MAX_N = 65536;
+// Steps 13-14 always run inside the next SpMV's gather up to GATHER_MAX_N rows,
+// where the pass is a launch's latency, if A's rows are known to be short: its
+// sliced-ELL copy has at most GATHER_MAX_DIAG diagonals, so no row stores more
+// (distinct) entries than that.  A step in us, gather and pass, fp16 basis
+// with Jacobi: 27-point rows 33.9 and 35.5 at 4096 rows, 38.4 and 39.4 at
+// 64,000; 7-point rows 30.7 and 33.6, 34.1 and 37.3.  The gather divides per
+// entry in the row's chain, so one long row undoes that: rows of 13 with one
+// of 20,000 (65,536 rows, CSR) 1378 and 1187, with 16 of 2000 (sliced-ELL) 440
+// and 238; scattered rows of 70 (CSR) 67 and 58, of 200 129 and 98.
+constexpr int GATHER_MAX_N = 65536, GATHER_MAX_DIAG = 32;
 
 struct DoneWatch {
     hipEvent_t ev[2] = {nullptr, nullptr};
@@ -450,10 +458,10 @@ int cbgmres_solve(const cbg_csr *A, const double *b, double *x, const cbg_opts *
         ((opt->flags & CBG_FLAG_NORMALISE_PASS) != 0 ||
          ((opt->flags & CBG_FLAG_NORMALISE_GATHER) == 0 &&
           ((double)A->nnz > 12.0 * n || pc0 == CBG_PC_JACOBI)));
-    // up to GATHER_MAX_N rows the pass would be a launch's latency (4 us), and
-    // the divisions hide behind the gather's loads: the gather forms the same
-    // bits there unless the pass was asked for
-    const bool pass = norm_pass && (n > GATHER_MAX_N || (opt->flags & CBG_FLAG_NORMALISE_PASS));
+    // small systems of short rows do without the pass's launch unless it was
+    // asked for: the gather forms the same bits
+    const bool gather_small = n <= GATHER_MAX_N && has_dix(A) && A->sell_ndiag <= GATHER_MAX_DIAG;
+    const bool pass = norm_pass && (!gather_small || (opt->flags & CBG_FLAG_NORMALISE_PASS));
     // steps whose update and re-dot share one basis pass
     auto fused = [&](int j) { return !gram && fuse && fused_takes(fmt, basis_ld(n), j); };
     ByteModel bm{(double)n, (double)A->nnz, (double)fmt_bytes(fmt)};
