@@ -484,8 +484,9 @@ __global__ __launch_bounds__(BLK) void k_spmv(int n, int64_t ldy, const int32_t 
     // gather and barrier, so a batch is as large as the block's rows at the
     // mean length fill it: eight for 256 rows of a 7-point matrix (36.1
     // against 38.1 us with four at 128^3), seven for 64 27-point rows (6.75
-    // per thread, 154 against 159 us; eight loads more than it uses, 162).
-    // Beyond that registers cost waves: sixteen took 238 us.
+    // per thread, 154 against 159 us; eight loads more than it uses, 162),
+    // four for 64 shorter rows (spmv_shape_of).  Beyond that registers cost
+    // waves: sixteen took 238 us.
     constexpr int UNR = RPB >= 256 ? 8 : CAP == 3072 ? 7 : 4;
     __shared__ double prod[CAP];
     __shared__ int lrp[RPB + 1];
@@ -3066,17 +3067,22 @@ static int grid_for(int64_t work_items, int per_block)
 
 // Launch shape of the CSR-stream SpMV from the mean row length: rows per
 // block and the LDS product buffer (entries), sized so a block's products
-// fit it at up to about 8, 48 and 64 entries per row.  64 rows of up to 30
-// entries on average take 3072: 64 uneven rows often hold more than the
-// 2048 that 27-point rows need, and such a block sums its rows one gather
-// at a time.  1,000,003 rows of 4 to 82 entries (26 on average): 128 us
-// against 135 with 2048; 27-point rows at 128^3 do not change (154, 153).
-// 4096 lets fewer blocks share a CU: 124 and 173.
+// fit it at up to about 8, 32 (48 with 3072), 64 and 128 entries per row.
+// 64 rows of 20 to 28 entries on average fill one batch of seven products a
+// thread but two of four, and take 3072 entries: 64 uneven rows often hold
+// more than the 2048 that 27-point rows need, and such a block sums its rows
+// one gather at a time.  1,000,003 rows of 4 to 82 entries (26 on average):
+// 128 us against 135 with 2048; 27-point rows at 128^3 do not change (154,
+// 153); 4096 lets fewer blocks share a CU: 124 and 173.  Shorter rows would
+// issue loads that the batch of seven does not use, longer ones take two of
+// them: 1,000,003 rows of 8, four and seven: 26.6 and 38.8 us, of 14 32.5 and
+// 40.7, of 16 38.6 and 42.3, of 20 43.8 and 44.4, of 22 59.4 and 54.8, of 27
+// 76.1 and 72.0, of 29 79.8 and 85.0.
 int spmv_shape_of(int n, int64_t nnz)
 {
     double avg = n > 0 ? (double)nnz / n : 1.0;
     if (avg <= 7.5) return SPMV_R256_C2K;
-    if (avg <= 30.0) return SPMV_R64_C3K;
+    if (avg <= 30.0) return avg > 20.0 && avg <= 28.0 ? SPMV_R64_C3K : SPMV_R64_C2K;
     if (avg <= 60.0) return SPMV_R64_C4K;
     return SPMV_R32_C4K;
 }
@@ -3253,6 +3259,7 @@ int launch_spmv(const SpmvArgs &a, hipStream_t s)
         return spmv_sell(a, s);
     switch (a.sg) {
     case SPMV_R256_C2K: return spmv_shape<256, 2048>(a, s);
+    case SPMV_R64_C2K: return spmv_shape<64, 2048>(a, s);
     case SPMV_R64_C3K: return spmv_shape<64, 3072>(a, s);
     case SPMV_R64_C4K: return spmv_shape<64, 4096>(a, s);
     case SPMV_RP64_C2K: return spmv_rp_shape<64, 2048>(a, s);

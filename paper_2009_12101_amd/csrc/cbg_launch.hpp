@@ -79,7 +79,8 @@ enum { RR_NB = 0, RR_SCALE = 1, RR_NORM2 = 2, RR_RESID = 3, RR_H = 4, RR_U = 5, 
 
 // SpMV launch shapes: rows per block and LDS product-buffer entries
 enum { SPMV_R256_C2K = 0, SPMV_R64_C3K = 1, SPMV_R64_C4K = 2, SPMV_R32_C4K = 3,
-       SPMV_RP64_C2K = 4 };   // row-parallel gather (k_spmv_rp)
+       SPMV_RP64_C2K = 4,    // row-parallel gather (k_spmv_rp)
+       SPMV_R64_C2K = 5 };
 int spmv_shape_of(int n, int64_t nnz);     // from the mean row length
 int spmv_rows(int shape);
 int spmv_grid(int shape, int64_t ldy);
