@@ -1416,7 +1416,7 @@ __device__ void block_fold2(const double *__restrict__ s0, const double *__restr
 
 // block_fold of nb <= SMALL_TILES sums by one thread, in the same order: each
 // quarter as the wave butterfly leaves it on lane 0, then the quarters.
-constexpr int SMALL_TILES = 8;
+constexpr int SMALL_TILES = 8;           // what it can fold
 __device__ __forceinline__ double thread_fold(const double *__restrict__ src, int nb)
 {
     constexpr int Q = SMALL_TILES / RWAVES;              // partials of a quarter, at most
@@ -1533,11 +1533,23 @@ __device__ __forceinline__ void gram_times_h(const double *__restrict__ G, size_
 // keeps the blocks of a full grid closer together in the basis: at 128^3
 // fp16, 512 tiles, j to 100, 43.7 us shallow, 49.3 us deep, 43.2 us before.
 //
-// RU_SMALL (U_CGS2 with `close` on at most SMALL_TILES tiles, where a step is
+// RU_SMALL (U_CGS2 with `close` on at most small_tiles() tiles, where a step is
 // launches and their latency): the prologue also folds the multi-dot's and
 // the SpMV's partials, which saves that launch (5 us); each of a tile's CH
 // chunks has a block of its own; and the block that finishes last forms all
 // norms from w, tile by tile in the order of the other forms (same bits).
+// That tail takes 0.7 us a tile of 2048 fp64 rows, 1.7 of 4096 rows, and an
+// e4m3 tile is one chunk, streamed by one block.  A step of 7-point rows with
+// 60 vectors in us, small and general: fp64 26.4 and 32.0 with one tile, 34.4
+// and 35.9 with seven, 33.6 and 31.2 with eight; fp32 30.7 and 31.9 with three,
+// 31.7 and 31.6 with four; fp16 32.8 and 34.8 with two, 36.4 and 33.5 with
+// four; e4m3 40.1 and 36.3 with one, 59.0 and 35.9 with eight.
+template <int F> constexpr int small_tiles()
+{
+    return F == F_FP64 ? 7 : F == F_E4M3 ? 0 : Fmt<F>::VW == 4 ? 3 : 2;
+}
+static_assert(small_tiles<F_FP64>() <= SMALL_TILES, "thread_fold's range");
+
 enum { RU_SHALLOW = 0, RU_DEEP = 1, RU_SMALL = 2 };
 
 template <int F, int ROLE, int MODE>
@@ -1749,7 +1761,7 @@ __global__ __launch_bounds__(BLK) void k_update(const uint8_t *__restrict__ V, i
             // The SpMV's partials, a quarter per wave and a lane's in turn, as in
             // the fold that this replaces.  Up to 256 of them are one per lane,
             // in flight with the multi-dot's; the CSR kernels leave one per 64
-            // rows, or per 32 long ones: up to 512 or 1024 on a small step.
+            // rows, or per 32 long ones: up to 448 on a small step.
             const int q4 = (nb_spmv + RWAVES - 1) / RWAVES;
             const int lo = min(wv * q4, nb_spmv), cnt = min(q4, nb_spmv - lo);
             double om = lane < cnt ? spmv_part[lo + lane] : 0.0;
@@ -3394,7 +3406,32 @@ void launch_multidot(const OrthArgs &a, hipStream_t s)
 #undef CBG_MD
 }
 
-bool small_step(int fmt, int64_t n) { return orth_grid(fmt, n) <= SMALL_TILES; }
+bool small_step(int fmt, int64_t n)
+{
+    int most = 0;
+    CBG_FMT_SWITCH(fmt, (most = small_tiles<F>()))
+    return orth_grid(fmt, n) <= most;
+}
+
+template <int F>
+static void update_small(const OrthArgs &a, int g0, const RedArgs &ra, const StepArrays &sa,
+                         hipStream_t s)
+{
+    if constexpr (small_tiles<F>() > 0) {
+        const dim3 g(g0 * Fmt<F>::CH + 1);
+        const uint8_t *V = (const uint8_t *)a.V;
+        if (a.ev0)
+            hipExtLaunchKernelGGL((k_update<F, U_CGS2, RU_SMALL>), g, dim3(BLK), 0, s, a.ev0,
+                                  a.ev1, 0, V, a.ld, a.scales, a.n, a.j, a.coef, a.wio, a.dinv,
+                                  ra, a.st, a.u, a.stw, a.G, sa, g0, a.close, a.ws.spmv,
+                                  a.nb_spmv);
+        else
+            k_update<F, U_CGS2, RU_SMALL><<<g, BLK, 0, s>>>(V, a.ld, a.scales, a.n, a.j, a.coef,
+                                                            a.wio, a.dinv, ra, a.st, a.u, a.stw,
+                                                            a.G, sa, g0, a.close, a.ws.spmv,
+                                                            a.nb_spmv);
+    }
+}
 
 void launch_update(const OrthArgs &a, hipStream_t s)
 {
@@ -3428,10 +3465,7 @@ void launch_update(const OrthArgs &a, hipStream_t s)
         CBG_UPDL(R, RU_SHALLOW)                                                               \
     }
     if (a.nb_spmv > 0) {                                        // a small step (small_step)
-        int ch = 1;
-        CBG_FMT_SWITCH(a.fmt, (ch = Fmt<F>::CH))
-        const int g = g0 * ch + 1;
-        CBG_UPDL(U_CGS2, RU_SMALL)
+        CBG_FMT_SWITCH(a.fmt, (update_small<F>(a, g0, ra, sa, s)))
         return;
     }
     switch (a.role) {

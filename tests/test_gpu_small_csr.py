@@ -1,16 +1,15 @@
 """Small steps on the CSR arrays, where the SpMV leaves many partials.
 
-Steps of up to eight tiles fold the SpMV's partials of omega^2 =
-||A M^-1 v||^2 inside the update.  Without a sliced-ELL copy the SpMV runs one
-block per 64 rows (one per 32 rows beyond 60 entries a row on average), up to
-512 or 1024 partials at the largest small step: at, below and above the 64
-that a lane of each of the four waves takes at once (256 partials), at the
-last small step (32,768 rows of the 8- and 16-bit formats, 16,384 of the
-others) and one row beyond it.
+Small steps fold the SpMV's partials of omega^2 = ||A M^-1 v||^2 inside the
+update.  Without a sliced-ELL copy the SpMV runs one block per 64 rows (one
+per 32 rows beyond 60 entries a row on average): up to 448 partials on the
+largest small step (14,336 rows of fp64), and 512 or 1024 on a step of eight
+tiles.  Below, at and above the 64 that a lane of each of the four waves takes
+at once (256 partials), on the last small step and beyond it.
 
-A lost partial shows in step 7's test, in t1^2 = omega^2 - h^T h - h^T u and
-so in h_{j+1,j}: three steps, before stored entries can round differently,
-follow the oracle's Fig. 1 with residuals and x to 1e-12 and the same count of
+A lost partial shows in step 7's test and in t1^2 = omega^2 - h^T h - h^T u:
+three steps, before stored entries can round differently, follow the oracle's
+Fig. 1 with residuals and x to 1e-12 and the same count of
 re-orthogonalisations; none of them is hard (t1 stays above 0.2 omega on these
 systems), and they take the same forms as on the sliced-ELL copy, which has a
 quarter of the partials.
@@ -63,9 +62,11 @@ SYSTEMS = {
     "rows26_20000": lambda P: random_rows(20000, 26, 3),
     "rows26_32768": lambda P: random_rows(32768, 26, 4),
     "rows26_32769": lambda P: random_rows(32769, 26, 5),
-    # long rows, 32 rows a block: 256, 264, 512 and 1024
+    # long rows, 32 rows a block: 256, 264, 448, (not small) 456, 512 and 1024
     "rows70_8192": lambda P: random_rows(8192, 70, 6),
     "rows70_8448": lambda P: random_rows(8448, 70, 7),
+    "rows70_14336": lambda P: random_rows(14336, 70, 10),
+    "rows70_14592": lambda P: random_rows(14592, 70, 11),
     "rows70_16384": lambda P: random_rows(16384, 70, 8),
     "rows70_32768": lambda P: random_rows(32768, 70, 9),
 }
@@ -79,7 +80,8 @@ SYSTEMS = {
     ("rows26_20000", "bf16", "none"), ("rows26_32768", "e4m3", "none"),
     ("rows26_32769", "fp16", "none"),
     ("rows70_8192", "fp64", "none"), ("rows70_8448", "fp64", "none"),
-    ("rows70_16384", "fp64", "jacobi"), ("rows70_16384", "fp32", "none"),
+    ("rows70_14336", "fp64", "none"), ("rows70_14336", "fp64", "jacobi"),
+    ("rows70_14592", "fp64", "none"), ("rows70_16384", "fp64", "jacobi"), ("rows70_16384", "fp32", "none"),
     ("rows70_32768", "fp16", "none"), ("rows70_32768", "fp16", "jacobi")])
 def test_omega_counts_every_partial(orc, dev, system, fmt, precond):
     import paper_2009_12101_amd as cbg
