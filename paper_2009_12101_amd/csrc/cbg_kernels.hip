@@ -3339,21 +3339,33 @@ int orth_grid(int fmt, int64_t n)
 
 // The multi-dot's launch: how many stored vectors a block takes (a multiple
 // of the batch kc), and LDS padding that limits a CU to two blocks.  Three
-// blocks fit a CU by registers.  Up to 512 blocks the time is set by the
-// slowest block's loads, so more, shorter blocks win; beyond three per CU the
-// blocks run in rounds, each as long as its blocks.  Each block reads its
-// tile of w (and of the newest vector) besides its chunk, `extra` vectors'
-// worth.  The choice minimises rounds x blocks per round x vectors per block:
-// 132 int16 tiles at j = 50 run in 4 chunks (34 us before, 11 us now); 1000
-// fp16 tiles at j to 200 in one chunk, two per CU (two even rounds, 138 us;
-// three per CU leave a second round of 232 blocks, 154 us; before 141 us).
+// blocks fit a CU by registers, four without the Gram row.  Up to 512 blocks
+// the time is set by the slowest block's loads, so more, shorter blocks win;
+// beyond three per CU the blocks run in rounds, each as long as its blocks.
+// Each block reads its tile of w (and of the newest vector) besides its
+// chunk, `extra` vectors' worth.  The choice minimises rounds x blocks per
+// round x vectors per block: 132 int16 tiles at j = 50 run in 4 chunks (34 us
+// before, 11 us now); 1000 fp16 tiles at j to 200 in one chunk, two per CU
+// (two even rounds, 138 us; three per CU leave a second round of 232 blocks,
+// 154 us; before 141 us).  Without the Gram row, 1000 fp16 tiles at j = 100:
+// 137 us two per CU, 145 with the Gram form's padding, which leaves three.  An
+// e4m3 tile is one chunk, half the loads in flight per block, and takes no
+// padding: 1000 tiles, j to 100, 53.6 us a step without and 57.3 with it.
 constexpr int FULL_GRID = 512;
 struct MdotShape {
     int chunk, pad;
 };
-static MdotShape multidot_shape(int tiles, int j, int kc, int eb)
+template <bool GRAM> constexpr int multidot_pad()
 {
-    constexpr int SLOTS = 768, PAD = 24576;
+    constexpr int LDS = 160 * 1024, PAD = GRAM ? 24576 : 40960;
+    constexpr int SUMS = NWAVE * (GRAM ? 2 : 1) * (MAX_RESTART + 1) * (int)sizeof(double);
+    static_assert(3 * (SUMS + PAD) > LDS && 2 * (SUMS + PAD + 1024) <= LDS, "two blocks per CU");
+    static_assert(SUMS + PAD + 1024 <= 64 * 1024, "LDS of a launch");
+    return PAD;
+}
+static MdotShape multidot_shape(int tiles, int j, int kc, int eb, bool gram)
+{
+    constexpr int SLOTS = 768;
     const int batches = (j + kc - 1) / kc;
     const double extra = 1.0 + 8.0 / eb;
     MdotShape best{batches * kc, 0};
@@ -3373,7 +3385,8 @@ static MdotShape multidot_shape(int tiles, int j, int kc, int eb)
     const double two = (double)((tiles + FULL_GRID - 1) / FULL_GRID) * FULL_GRID *
                        (batches * kc + extra);
     if (two < cost)
-        best = {batches * kc, PAD};
+        best = {batches * kc,
+                eb == 1 ? 0 : gram ? multidot_pad<true>() : multidot_pad<false>()};
     return best;
 }
 
@@ -3383,7 +3396,7 @@ void launch_multidot(const OrthArgs &a, hipStream_t s)
 {
     const int tiles = orth_grid(a.fmt, a.n);
     MdotShape sh{};
-    CBG_FMT_SWITCH(a.fmt, (sh = multidot_shape(tiles, a.j, Fmt<F>::KC, fmt_bytes(F))))
+    CBG_FMT_SWITCH(a.fmt, (sh = multidot_shape(tiles, a.j, Fmt<F>::KC, fmt_bytes(F), a.gram)))
     const dim3 g(tiles, (a.j + sh.chunk - 1) / sh.chunk);
     RedArgs ra{a.ws.orth, a.ws.stride};
     const uint8_t *V = (const uint8_t *)a.V;
