@@ -375,10 +375,11 @@ __device__ __forceinline__ int bitrev(int l)
 
 // Block partials of a reduction, value-major: value v of block b at
 // part[v * stride + b].  A producer kernel writes its block's values with
-// plain stores; a one-block reduce kernel launched after it (the kernel
-// boundary makes the writes visible) folds them in block order.  No block
-// waits for or fences against another, and the sums are bitwise
-// reproducible.
+// plain stores, and a kernel launched after it (the boundary makes the writes
+// visible) folds them in block order; where the launch's own last block folds
+// them instead (the close of the one-pass update), they are passed by
+// agent-scope stores and loads and a ticket.  No block waits for another, and
+// the sums are bitwise reproducible.
 struct RedArgs {
     double *part;
     int stride;          // >= the producer's grid size

@@ -15,8 +15,8 @@
 // Steps of few tiles leave the reduce to the update too (RU_SMALL).  A step
 // whose norm cannot come from Pythagoras (a hard step) gets an explicit
 // second pass: the first one pauses the cycle for the host to enqueue it,
-// from then on every step carries it (U_HARD, nothing on other steps).  Producers write block partials
-// with plain stores; a kernel launched later, or the block that finishes
+// from then on every step carries it (U_HARD, nothing on other steps).
+// Producers write block partials; a kernel launched later, or the block that finishes
 // last, folds them in fixed order, so sums are bitwise reproducible.
 // The host only enqueues kernels; it synchronises once per restart cycle,
 // and once more in the cycle that meets a solve's first hard step.
@@ -1284,8 +1284,7 @@ __global__ __launch_bounds__(BLK) CBG_MD_ATTR void k_multidot(const uint8_t *__r
 //   ||w||_inf (partials in rows 0 and 1, except U_STEP1);
 //   U_CGS2: steps 5-10 in one update (coef = h; see below).
 //   U_SOLUTION: x += dinv .* s (Jacobi) or x += s;  U_COMBINE: out = s.
-// Full tiles stream the vectors UNR at a time with the next batch's loads
-// in flight while the current batch is decoded and accumulated.
+// The vectors stream through a ring of register batches (see k_update).
 // ---------------------------------------------------------------------------
 
 // Fixed-order folds of block partials (used by the reduce kernel and by

@@ -723,7 +723,7 @@ __global__ __launch_bounds__(256) void k_grad_o(int n, const int32_t *__restrict
 // by DPP.  Bound by those gathers from L2 (64 bytes an entry of fp16 vectors,
 // 256 of fp64): at 64^3 and K = 32 the products took 245, 295, 304 and (the
 // gradient's dots) 421 us with a lane per value, one entry of two rows per
-// instruction; 67, 127 and, the last two in one kernel, 127 us now.  With
+// instruction; 67, 120 and, the last two in one kernel, 128 us now.  With
 // the network's output instead of P's values the first product also forms
 // P, and with dO the last one forms dL/dO, which saves P, dL/dP and two more
 // passes over A (117 us).
@@ -1081,7 +1081,7 @@ __global__ void k_loss_fold(const double *__restrict__ part, int nb, double scal
 // one contiguous 128-byte read, and nothing goes through LDS but the weights.
 // Latency-bound with one wave per SIMD (160 accumulators a lane), so the next
 // tile's loads run under the current tile's 72 products: 386 us at 262,144
-// rows with the tile staged in LDS value by value, 101 us now (the fold of the
+// rows with the tile staged in LDS value by value, 56 us now (the fold of the
 // blocks' partials took 124 us with 512 of them in turn per parameter).
 // ---------------------------------------------------------------------------
 
