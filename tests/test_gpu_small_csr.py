@@ -62,6 +62,11 @@ SYSTEMS = {
     "rows26_20000": lambda P: random_rows(20000, 26, 3),
     "rows26_32768": lambda P: random_rows(32768, 26, 4),
     "rows26_32769": lambda P: random_rows(32769, 26, 5),
+    # the last small step of the 4-byte and of the 16-bit formats, and beyond
+    "rows26_6144": lambda P: random_rows(6144, 26, 12),
+    "rows26_6145": lambda P: random_rows(6145, 26, 13),
+    "rows26_8192": lambda P: random_rows(8192, 26, 14),
+    "rows26_8193": lambda P: random_rows(8193, 26, 15),
     # long rows, 32 rows a block: 256, 264, 448, (not small) 456, 512 and 1024
     "rows70_8192": lambda P: random_rows(8192, 70, 6),
     "rows70_8448": lambda P: random_rows(8448, 70, 7),
@@ -79,6 +84,10 @@ SYSTEMS = {
     ("rows26_16384", "fp16", "none"), ("rows26_16385", "fp16", "none"),
     ("rows26_20000", "bf16", "none"), ("rows26_32768", "e4m3", "none"),
     ("rows26_32769", "fp16", "none"),
+    ("rows26_6144", "fp32", "none"), ("rows26_6144", "int32", "none"),
+    ("rows26_6145", "fp32", "none"), ("rows26_6145", "int32", "jacobi"),
+    ("rows26_8192", "fp16", "none"), ("rows26_8192", "int16", "none"),
+    ("rows26_8193", "fp16", "none"), ("rows26_8193", "fp16s", "none"),
     ("rows70_8192", "fp64", "none"), ("rows70_8448", "fp64", "none"),
     ("rows70_14336", "fp64", "none"), ("rows70_14336", "fp64", "jacobi"),
     ("rows70_14592", "fp64", "none"), ("rows70_16384", "fp64", "jacobi"), ("rows70_16384", "fp32", "none"),
